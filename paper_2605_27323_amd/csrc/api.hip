@@ -55,6 +55,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 constexpr int kMaxPools = 4;  // concurrent pools of a batched launch
 constexpr uint32_t kTailWavesPerCu = 16;  // the hybrid tail kernel runs 4 waves per SIMD
+constexpr uint32_t kSimdsPerCu = 4;
 
 struct StageTimer {
     int stage;
@@ -339,6 +340,7 @@ pt_status enqueue_stages(pt_ctx* c, const pt_render_args* a, const Launch& L, co
         wb.sort_key = reinterpret_cast<uint32_t*>(base + w.sort_key);
         wb.perm = reinterpret_cast<uint32_t*>(base + w.perm);
         wb.hist = reinterpret_cast<uint32_t*>(base + w.hist);
+        wb.simds = (uint32_t)c->num_cu * kSimdsPerCu;
         if (rec) {
             wb.rec_hit = rec->hit;
             wb.rec_vis = rec->vis;
@@ -1230,6 +1232,7 @@ BatchBufs batch_bufs(const BatchPlan& P, char* base, int n) {
     bb.hit = pool + 6 * C;
     bb.sh_o = pool + 7 * C; bb.sh_d = pool + 8 * C; bb.sh_c = pool + 9 * C;
     bb.L = reinterpret_cast<float4*>(base + P.o_L);
+    bb.simds = (uint32_t)P.num_cu * kSimdsPerCu;
     return bb;
 }
 

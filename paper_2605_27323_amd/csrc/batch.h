@@ -51,6 +51,7 @@ struct BatchBufs {
     float4* sh_d;
     float4* sh_c;
     float4* L;            // [total] by global path id
+    uint32_t simds;       // SIMDs of the device
 };
 
 PT_DEV uint32_t meta_pack(uint32_t k, uint32_t smooth, uint32_t job) { return k | (smooth << 16) | (job << 24); }

@@ -64,16 +64,17 @@ __global__ void __launch_bounds__(256) k_batch_regen(BatchBufs bb, int q) {
         batch_regen_item(bb, q, i);
 }
 
-// persistent traversal over the pool (see k_extend): each wave owns a chunk
-// of the queue and refills finished lanes from it; a lane's scene is its
+// persistent traversal over the pool (see k_extend); a lane's scene is its
 // path's job's scene
 template <int LDS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
 k_batch_extend(BatchBufs bb, int q, uint2* __restrict__ ovf, int gcap) {
     extern __shared__ __align__(8) uint32_t smem[];
     TravStack<LDS> st = stack_b<LDS>(smem, ovf, gcap);
-    uint32_t next, end;
-    wave_chunk(bb.ctl->count, next, end);
+    __shared__ uint32_t cursor;
+    const BlockShare share = open_share(bb.ctl->count, bb.simds, &cursor);
+    bool more = share.at(0u) < share.hi;
+    uint32_t want = share.start;
     bool live = false;
     uint32_t item = 0, ref = 0;
     SceneView sc{};
@@ -82,10 +83,12 @@ k_batch_extend(BatchBufs bb, int q, uint2* __restrict__ ovf, int gcap) {
     while (true) {
         const uint64_t idle = __ballot(!live);
         const uint32_t nidle = (uint32_t)__popcll(idle);
-        if (next < end && (nidle >= kRefill || nidle == 64u)) {
+        if (more && (nidle >= kRefill || nidle == 64u)) {
+            const uint32_t n = min(nidle, want), c = share.take(n, more);
+            want = 64u;
             if (!live) {
-                const uint32_t i = next + rank_in(idle);
-                if (i < end) {
+                const uint32_t r = rank_in(idle), i = share.at(c + r);
+                if (r < n && i < share.hi) {
                     const float4 o4 = bb.ray_o[q][i], d4 = bb.ray_d[q][i];
                     sc = bb.jobs[f2u(bb.pst[q][i].w) >> 24].sc;
                     ray = make_ray(xyz(o4), xyz(d4));
@@ -94,10 +97,9 @@ k_batch_extend(BatchBufs bb, int q, uint2* __restrict__ ovf, int gcap) {
                     live = true;
                 }
             }
-            next = min(next + nidle, end);
         }
         if (__ballot(live) == 0ull) {
-            if (next < end) continue;
+            if (more) continue;
             break;
         }
         if (live && !closest_step<LDS>(sc, ray, INFINITY, h, ref, st)) {
@@ -143,8 +145,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
 k_batch_shadow(BatchBufs bb, uint2* __restrict__ ovf, int gcap) {
     extern __shared__ __align__(8) uint32_t smem[];
     TravStack<LDS> st = stack_b<LDS>(smem, ovf, gcap);
-    uint32_t next, end;
-    wave_chunk(bb.ctl->shadow, next, end);
+    __shared__ uint32_t cursor;
+    const BlockShare share = open_share(bb.ctl->shadow, bb.simds, &cursor);
+    bool more = share.at(0u) < share.hi;
+    uint32_t want = share.start;
     bool live = false;
     uint32_t item = 0, ref = 0, tag = 0;
     SceneView sc{};
@@ -152,10 +156,12 @@ k_batch_shadow(BatchBufs bb, uint2* __restrict__ ovf, int gcap) {
     while (true) {
         const uint64_t idle = __ballot(!live);
         const uint32_t nidle = (uint32_t)__popcll(idle);
-        if (next < end && (nidle >= kRefill || nidle == 64u)) {
+        if (more && (nidle >= kRefill || nidle == 64u)) {
+            const uint32_t n = min(nidle, want), c = share.take(n, more);
+            want = 64u;
             if (!live) {
-                const uint32_t i = next + rank_in(idle);
-                if (i < end) {
+                const uint32_t r = rank_in(idle), i = share.at(c + r);
+                if (r < n && i < share.hi) {
                     const float4 o4 = bb.sh_o[i], d4 = bb.sh_d[i];
                     tag = f2u(d4.w);
                     sc = bb.jobs[tag & 0x7FFFFFFFu].sc;
@@ -165,10 +171,9 @@ k_batch_shadow(BatchBufs bb, uint2* __restrict__ ovf, int gcap) {
                     live = true;
                 }
             }
-            next = min(next + nidle, end);
         }
         if (__ballot(live) == 0ull) {
-            if (next < end) continue;
+            if (more) continue;
             break;
         }
         bool fin = false;

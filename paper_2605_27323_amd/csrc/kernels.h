@@ -51,6 +51,7 @@ struct WaveBufs {
     uint2* rec_hit;
     uint8_t* rec_vis;
     uint32_t rec_n;
+    uint32_t simds;  // SIMDs of the device (how thin a short queue is spread)
 };
 
 constexpr int kSortBins = 64;

@@ -40,29 +40,72 @@ __device__ __forceinline__ unsigned long long wave_broadcast_u64(unsigned long l
     return ((unsigned long long)hi << 32) | lo;
 }
 
-// Workgroup order in which consecutive parts of a queue are handed out.
-// The dispatcher places workgroup b on XCD b mod 8 (each XCD has its own
-// L2); with xcd_local the order b' = (b mod 8) * (G / 8) + b / 8 gives every
-// XCD one contiguous eighth of the queue, so that neighbouring rays (close
-// pixels, similar directions) share an L2 instead of being spread over all
-// eight.  Grids that are not a multiple of 8 keep launch order.
-__device__ __forceinline__ uint32_t block_order(int xcd_local) {
-    const uint32_t b = blockIdx.x;
-    if (!xcd_local || (gridDim.x & 7u) != 0u) return b;
-    return (b & 7u) * (gridDim.x >> 3) + (b >> 3);
-}
+// A workgroup's share of a queue in the persistent traversal kernels.  The
+// queue is cut into sections of 64 entries per wave that go to the
+// workgroups in turn, and the waves of a workgroup take their section's
+// entries, and then those of its next section, from one cursor in LDS.
+// Every workgroup then has rays from all over the queue (all over the image,
+// after raygen): with one contiguous part of the queue per wave, the waves
+// that got the empty sky ended long before those that got the objects.
+// Sections of 1024 entries gave 2.74 instead of 2.43 ms per frame of the
+// 1.02M-triangle scene, sections of 64 the same.  Full waves also where the
+// queue does not fill the grid: 65536 rays as 1024 waves of 64 took 247 us a
+// frame of the Cornell room, as waves of 32 255, of 16 279, of 8 (every wave
+// of the grid) 351.  Only a queue too short for one full wave per SIMD is cut
+// into sections of fewer entries per wave: such a wave is alone on its SIMD
+// and takes as many steps as its longest ray and their divergence ask for
+// (1536 rays: 218 us a frame, in full waves 228).
+// xcd_local (PT_FLAG_XCD_LOCAL): the dispatcher places workgroup b on XCD
+// b mod 8 (each XCD has its own L2); the sections of one eighth of the queue
+// go to the workgroups of one XCD, so that neighbouring rays share an L2.
+// Grids that are not a multiple of 8 ignore it.
+struct BlockShare {
+    uint32_t first;   // first entry of the workgroup's first section
+    uint32_t hi;      // end of the queue (of the XCD's eighth)
+    uint32_t stride;  // entries from one of its sections to the next
+    uint32_t lg;      // log2 of the entries of a section
+    uint32_t start;   // entries a wave takes first
+    __attribute__((address_space(3))) uint32_t* cursor;
 
-// The contiguous chunk [next, end) of a queue of `count` entries owned by
-// this wave in a persistent kernel (waves in block_order).
-__device__ __forceinline__ void wave_chunk(uint32_t count, uint32_t& next, uint32_t& end, int xcd_local = 0) {
-    const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t wave = (block_order(xcd_local) * blockDim.x + threadIdx.x) >> 6;
-    const uint32_t chunk = (uint32_t)(((uint64_t)count + nwaves - 1) / nwaves);
-    next = (uint32_t)min((uint64_t)wave * chunk, (uint64_t)count);
-    end = (uint32_t)min((uint64_t)next + chunk, (uint64_t)count);
-    // the same for every lane of the wave: keep them in scalar registers
-    next = __builtin_amdgcn_readfirstlane(next);
-    end = __builtin_amdgcn_readfirstlane(end);
+    // queue position of the share's c-th entry (valid below hi)
+    __device__ __forceinline__ uint32_t at(uint32_t c) const {
+        return first + (c >> lg) * stride + (c & ((1u << lg) - 1u));
+    }
+    // the next n entries of the share, for this wave: the index of the first
+    // (wave-uniform); more = false once the share holds no further ones
+    __device__ __forceinline__ uint32_t take(uint32_t n, bool& more) const {
+        uint32_t c = 0;
+        if (lane_id() == 0) c = __hip_atomic_fetch_add(cursor, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        c = __builtin_amdgcn_readfirstlane(c);
+        more = at(c + n) < hi;
+        return c;
+    }
+};
+
+// simds: SIMDs of the device.  Every thread of the workgroup calls this (it
+// synchronises the workgroup).
+__device__ __forceinline__ BlockShare open_share(uint32_t count, uint32_t simds, uint32_t* cursor, int xcd_local = 0) {
+    if (threadIdx.x == 0) *cursor = 0u;
+    uint32_t blk = blockIdx.x, nblk = gridDim.x, lo = 0u, hi = count;
+    if (xcd_local && (gridDim.x & 7u) == 0u) {
+        const uint32_t part = (count + 7u) >> 3;
+        lo = min((blk & 7u) * part, count);
+        hi = min(lo + part, count);
+        blk >>= 3;
+        nblk >>= 3;
+    }
+    uint32_t lg = 6u;  // log2 of the entries per wave
+    while (lg > 0u && (simds << (lg - 1u)) >= count) --lg;
+    BlockShare s;
+    s.start = 1u << lg;
+    for (uint32_t w = blockDim.x >> 6; w > 1u; w = (w + 1u) >> 1) ++lg;
+    s.lg = lg;
+    s.stride = __builtin_amdgcn_readfirstlane(nblk << lg);
+    s.first = __builtin_amdgcn_readfirstlane(lo + (blk << lg));
+    s.hi = __builtin_amdgcn_readfirstlane(hi);
+    s.cursor = (__attribute__((address_space(3))) uint32_t*)cursor;
+    __syncthreads();
+    return s;
 }
 
 // Block-aggregated reservation on two queue counters: every thread of the
