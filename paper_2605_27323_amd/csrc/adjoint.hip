@@ -53,7 +53,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k
     const uint32_t nlanes = gridDim.x * blockDim.x;
     const uint32_t gtid = blockIdx.x * blockDim.x + threadIdx.x;
     TravStack<LDS> st =
-        make_trav_stack<LDS>(reinterpret_cast<uint2*>(smem) + threadIdx.x, (int)blockDim.x, ovf, gtid, (int)nlanes, gcap);
+        make_trav_stack<LDS>(reinterpret_cast<uint2*>(smem), (int)blockDim.x, ovf, gtid, (int)nlanes, gcap);
     const uint32_t npaths = (uint32_t)cam.W * (uint32_t)cam.H * (uint32_t)pp.spp;
     uint32_t next = 0, end = 0;  // wave-uniform
     bool drained = false;        // wave-uniform
@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED
     const uint32_t nlanes = gridDim.x * blockDim.x;
     const uint32_t gtid = blockIdx.x * blockDim.x + threadIdx.x;
     TravStack<LDS> st =
-        make_trav_stack<LDS>(reinterpret_cast<uint2*>(smem) + threadIdx.x, (int)blockDim.x, ovf, gtid, (int)nlanes, gcap);
+        make_trav_stack<LDS>(reinterpret_cast<uint2*>(smem), (int)blockDim.x, ovf, gtid, (int)nlanes, gcap);
     __shared__ float light_g[3 * kLdsLights];
     __shared__ float hot_g[2 * 3 * kHotTris];
     AtomicAcc acc;

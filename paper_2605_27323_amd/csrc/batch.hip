@@ -11,7 +11,7 @@ namespace {
 
 template <int LDS>
 __device__ __forceinline__ TravStack<LDS> stack_b(uint32_t* smem, uint2* ovf, int gcap) {
-    return make_trav_stack<LDS>(reinterpret_cast<uint2*>(smem) + threadIdx.x, (int)blockDim.x, ovf,
+    return make_trav_stack<LDS>(reinterpret_cast<uint2*>(smem), (int)blockDim.x, ovf,
                                 blockIdx.x * blockDim.x + threadIdx.x, (int)(gridDim.x * blockDim.x), gcap);
 }
 
@@ -65,9 +65,10 @@ __global__ void __launch_bounds__(256) k_batch_regen(BatchBufs bb, int q) {
 }
 
 // persistent traversal over the pool (see k_extend); a lane's scene is its
-// path's job's scene
+// path's job's scene, held in registers: at seven waves per SIMD nothing
+// spills, at eight nine registers did (a batch of 8 scenes 2.49 and 2.82 ms)
 template <int LDS>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7)))
 k_batch_extend(BatchBufs bb, int q, uint2* __restrict__ ovf, int gcap) {
     extern __shared__ __align__(8) uint32_t smem[];
     TravStack<LDS> st = stack_b<LDS>(smem, ovf, gcap);
@@ -75,18 +76,17 @@ k_batch_extend(BatchBufs bb, int q, uint2* __restrict__ ovf, int gcap) {
     const BlockShare share = open_share(bb.ctl->count, bb.simds, &cursor);
     bool more = share.at(0u) < share.hi;
     uint32_t want = share.start;
-    bool live = false;
-    uint32_t item = 0, ref = 0;
+    uint32_t item = 0, ref = kDoneRef;  // a lane without a ray
     SceneView sc{};
     Ray ray;
     Hit h;
     while (true) {
-        const uint64_t idle = __ballot(!live);
+        const uint64_t idle = __ballot(ref == kDoneRef);
         const uint32_t nidle = (uint32_t)__popcll(idle);
         if (more && (nidle >= kRefill || nidle == 64u)) {
             const uint32_t n = min(nidle, want), c = share.take(n, more);
             want = 64u;
-            if (!live) {
+            if (ref == kDoneRef) {
                 const uint32_t r = rank_in(idle), i = share.at(c + r);
                 if (r < n && i < share.hi) {
                     const float4 o4 = bb.ray_o[q][i], d4 = bb.ray_d[q][i];
@@ -94,17 +94,14 @@ k_batch_extend(BatchBufs bb, int q, uint2* __restrict__ ovf, int gcap) {
                     ray = make_ray(xyz(o4), xyz(d4));
                     closest_begin<LDS>(INFINITY, h, ref, st);
                     item = i;
-                    live = true;
                 }
             }
-        }
-        if (__ballot(live) == 0ull) {
-            if (more) continue;
+        } else if (nidle == 64u) {
             break;
         }
-        if (live && !closest_step<LDS>(sc, ray, INFINITY, h, ref, st)) {
-            bb.hit[item] = make_float4(h.t, 0.f, 0.f, u2f(h.tri));
-            live = false;
+        if (ref != kDoneRef) {
+            closest_step<LDS>(sc, ray, INFINITY, h, ref, st);
+            if (ref == kDoneRef) bb.hit[item] = make_float4(h.t, 0.f, 0.f, u2f(h.tri));
         }
     }
     if (st.overflow) atomicOr(&bb.ctl->err, 1u);
@@ -141,7 +138,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 // persistent any-hit over the shadow records; the job counters are updated
 // every trip for the lanes whose record ended its path
 template <int LDS>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7)))
 k_batch_shadow(BatchBufs bb, uint2* __restrict__ ovf, int gcap) {
     extern __shared__ __align__(8) uint32_t smem[];
     TravStack<LDS> st = stack_b<LDS>(smem, ovf, gcap);
@@ -149,17 +146,17 @@ k_batch_shadow(BatchBufs bb, uint2* __restrict__ ovf, int gcap) {
     const BlockShare share = open_share(bb.ctl->shadow, bb.simds, &cursor);
     bool more = share.at(0u) < share.hi;
     uint32_t want = share.start;
-    bool live = false;
-    uint32_t item = 0, ref = 0, tag = 0;
+    uint32_t item = 0, ref = kDoneRef, tag = 0;  // a lane without a ray
     SceneView sc{};
     Ray ray;
+    uint32_t occluded = 0u;
     while (true) {
-        const uint64_t idle = __ballot(!live);
+        const uint64_t idle = __ballot(ref == kDoneRef);
         const uint32_t nidle = (uint32_t)__popcll(idle);
         if (more && (nidle >= kRefill || nidle == 64u)) {
             const uint32_t n = min(nidle, want), c = share.take(n, more);
             want = 64u;
-            if (!live) {
+            if (ref == kDoneRef) {
                 const uint32_t r = rank_in(idle), i = share.at(c + r);
                 if (r < n && i < share.hi) {
                     const float4 o4 = bb.sh_o[i], d4 = bb.sh_d[i];
@@ -167,20 +164,17 @@ k_batch_shadow(BatchBufs bb, uint2* __restrict__ ovf, int gcap) {
                     sc = bb.jobs[tag & 0x7FFFFFFFu].sc;
                     ray = make_ray(xyz(o4), xyz(d4));
                     any_begin<LDS>(ref, st);
+                    occluded = 0u;
                     item = i;
-                    live = true;
                 }
             }
-        }
-        if (__ballot(live) == 0ull) {
-            if (more) continue;
+        } else if (nidle == 64u) {
             break;
         }
         bool fin = false;
-        if (live) {
-            bool occluded = false;
-            if (!any_step<LDS>(sc, ray, kShadowTmax, ref, st, occluded)) {
-                live = false;
+        if (ref != kDoneRef) {
+            any_step<LDS>(sc, ray, kShadowTmax, ref, st, occluded);
+            if (ref == kDoneRef) {
                 if (!occluded) batch_shadow_add(bb, item);
                 fin = (tag >> 31) != 0u;
             }

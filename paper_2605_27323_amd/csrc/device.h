@@ -182,7 +182,7 @@ struct Ray {
     f3 o, d;
     f3 inv;  // 1/d for the slab test, components below 2^-80 in magnitude replaced by +-2^-80
     f3 oi;   // o * inv, rounded: slab distances are p * inv - oi, one fused multiply-add
-    uint32_t k;  // axis permutation of the watertight test: kx | ky << 2 | kz << 4
+    uint32_t kz;  // axis of the largest direction component; the watertight test's axes are kz + 1, kz + 2, kz
     float Sx, Sy, Sz;
 };
 
@@ -205,43 +205,50 @@ PT_DEV Ray make_ray(f3 o, f3 d) {
     return r;
 }
 
-// The watertight test's axis permutation and shear constants of direction d
+// v's components on the axes kz + 1, kz + 2 and kz (modulo 3)
+PT_DEV f3 permute3(f3 v, uint32_t kz) {
+    const bool k0 = kz == 0u, k1 = kz == 1u;
+    return mk3(k0 ? v.y : (k1 ? v.z : v.x), k0 ? v.z : (k1 ? v.x : v.y), k0 ? v.x : (k1 ? v.y : v.z));
+}
+
+// The watertight test's axes and shear constants of direction d.  The
+// published test exchanges the first two axes when the direction's largest
+// component is negative, which keeps the triangle's winding.  Each edge
+// function is a difference of two products that hold one second-axis
+// coordinate each, so flipping the sign of those coordinates (flip_second)
+// gives the exchanged difference to the bit, signed zeros included, and the
+// scaled depth and the determinant with it: one sign flip per vertex where
+// the exchange took four comparisons and three field extractions per leaf.
 PT_DEV void set_shear(Ray& r, f3 d) {
     float ax = fabsf(d.x), ay = fabsf(d.y), az = fabsf(d.z);
-    int kz = 0;
+    uint32_t kz = 0u;
     float m = ax;
     if (ay > m) {
-        kz = 1;
+        kz = 1u;
         m = ay;
     }
-    if (az > m) kz = 2;
-    int kx = kz == 2 ? 0 : kz + 1;
-    int ky = kx == 2 ? 0 : kx + 1;
-    float dkz = comp3(d, kz);
-    if (dkz < 0.0f) {
-        int t = kx;
-        kx = ky;
-        ky = t;
-    }
-    r.k = (uint32_t)kx | ((uint32_t)ky << 2) | ((uint32_t)kz << 4);
-    r.Sx = comp3(d, kx) / dkz;
-    r.Sy = comp3(d, ky) / dkz;
-    r.Sz = 1.0f / dkz;
+    if (az > m) kz = 2u;
+    const f3 p = permute3(d, kz);
+    r.kz = kz;
+    r.Sx = p.x / p.z;
+    r.Sy = p.y / p.z;
+    r.Sz = 1.0f / p.z;
 }
+
+PT_DEV float flip_second(const Ray& r, float y) { return u2f(f2u(y) ^ (f2u(r.Sz) & 0x80000000u)); }
 
 // Returns true on a hit with t > 0: t, and the barycentrics of v1 and v2
 // undivided, as Vn / det and Wn / det (the traversal divides only for the
 // hit it keeps).
 PT_DEV bool tri_test(const Ray& r, f3 v0, f3 v1, f3 v2, float& t, float& Vn, float& Wn, float& dn) {
-    const int kx = (int)(r.k & 3u), ky = (int)((r.k >> 2) & 3u), kz = (int)(r.k >> 4);
-    f3 A = sub3(v0, r.o), B = sub3(v1, r.o), C = sub3(v2, r.o);
-    float Akz = comp3(A, kz), Bkz = comp3(B, kz), Ckz = comp3(C, kz);
-    float Ax = comp3(A, kx) - r.Sx * Akz;
-    float Ay = comp3(A, ky) - r.Sy * Akz;
-    float Bx = comp3(B, kx) - r.Sx * Bkz;
-    float By = comp3(B, ky) - r.Sy * Bkz;
-    float Cx = comp3(C, kx) - r.Sx * Ckz;
-    float Cy = comp3(C, ky) - r.Sy * Ckz;
+    const f3 A = permute3(sub3(v0, r.o), r.kz), B = permute3(sub3(v1, r.o), r.kz), C = permute3(sub3(v2, r.o), r.kz);
+    float Akz = A.z, Bkz = B.z, Ckz = C.z;
+    float Ax = A.x - r.Sx * Akz;
+    float Ay = flip_second(r, A.y - r.Sy * Akz);
+    float Bx = B.x - r.Sx * Bkz;
+    float By = flip_second(r, B.y - r.Sy * Bkz);
+    float Cx = C.x - r.Sx * Ckz;
+    float Cy = flip_second(r, C.y - r.Sy * Ckz);
     float U = Cx * By - Cy * Bx;
     float V = Ax * Cy - Ay * Cx;
     float W = Bx * Ay - By * Ax;
@@ -252,19 +259,16 @@ PT_DEV bool tri_test(const Ray& r, f3 v0, f3 v1, f3 v2, float& t, float& Vn, flo
         W = (float)((double)Bx * (double)Ay - (double)By * (double)Ax);
     }
     if ((U < 0.0f || V < 0.0f || W < 0.0f) && (U > 0.0f || V > 0.0f || W > 0.0f)) return false;
-    float det = (U + V) + W;
-    if (det == 0.0f) return false;
+    const float det = (U + V) + W;
     float Az = r.Sz * Akz;
     float Bz = r.Sz * Bkz;
     float Cz = r.Sz * Ckz;
     float T = (U * Az + V * Bz) + W * Cz;
-    float tt = T / det;
-    if (!(tt > 0.0f)) return false;
-    t = tt;
+    t = T / det;
     Vn = V;
     Wn = W;
     dn = det;
-    return true;
+    return (det != 0.0f) & (t > 0.0f);
 }
 
 // Returns true on a hit with t > 0; t and the barycentrics of v1, v2.
@@ -277,33 +281,34 @@ PT_DEV bool tri_intersect(const Ray& r, f3 v0, f3 v1, f3 v2, float& t, float& b1
 }
 
 // ---------------------------------------------------------------------------
-// traversal stack: per-lane entries in LDS (stride = block size, so the 64
-// lanes of a wave hit 64 consecutive 8-byte words), deeper entries spill to
-// a per-lane global area (stride = number of lanes).  The LDS pointer
-// carries the local address space so that pushes and pops compile to
-// ds_write_b64 / ds_read_b64 rather than flat accesses.
+// traversal stack: per-lane entries in LDS, deeper entries spill to a
+// per-lane global area (stride = number of lanes).
 //
-// Each lane owns LDS + 1 LDS entries: entry LDS is a discard slot.  A node
-// visit pushes its (up to three) farther children with push3, which writes
-// all three candidates without branches, the invalid ones into the discard
-// slot, as long as no lane of the wave is within three entries of the LDS
-// limit (a wave-uniform test); otherwise it takes the per-entry path that
-// spills to global memory.
+// The LDS entries of a wave are together: entry k of lane l at byte
+// 512 k + 8 l of the wave's area, so that the 64 lanes hit 64 consecutive
+// 8-byte words and the next entry is a constant away.  The stack pointer is
+// the LDS address of the next free entry: a push or a pop is one access and
+// one addition, and "empty" and "near the limit" are comparisons with a
+// wave-uniform address (the lanes' own offsets stay below one entry row).
+// It keeps counting past the LDS entries, where it only numbers the spilled
+// ones.  With entries a block apart, and the pointer a number, a push took
+// a select, a multiplication, a shift and an addition per entry.
+//
+// Each lane owns LDS + 1 LDS entries; the last one is not used.
 // ---------------------------------------------------------------------------
 #if defined(__HIP_DEVICE_COMPILE__)
 typedef __attribute__((address_space(3))) uint2 lds_uint2;
-// product of two values below 2^24 (full-rate 24-bit multiply on the GPU)
-__device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return __umul24(a, b); }
+constexpr uint32_t kStackRow = 64u * 8u;  // bytes from an entry to the next one of its lane
+__device__ __forceinline__ uint2 lds_entry(uint32_t at) { return *reinterpret_cast<lds_uint2*>(at); }
+__device__ __forceinline__ void lds_entry_set(uint32_t at, uint2 e) { *reinterpret_cast<lds_uint2*>(at) = e; }
 // true when the condition holds on no active lane of the wave
 __device__ __forceinline__ bool wave_none(bool c) { return __ballot(c) == 0ull; }
 #else
-typedef uint2 lds_uint2;
-inline uint32_t mul24(uint32_t a, uint32_t b) { return (a & 0xFFFFFFu) * (b & 0xFFFFFFu); }
+constexpr uint32_t kStackRow = 8u;
 inline bool wave_none(bool c) { return !c; }
 #endif
 
-// LDS bytes of a block's traversal stacks: LDS entries plus the discard slot
-// per lane, 8 bytes each
+// LDS bytes of a block's traversal stacks: LDS + 1 entries of 8 bytes per lane
 PT_DEV constexpr size_t trav_stack_lds_bytes(int lds, int block) {
     return (size_t)(lds + 1) * sizeof(uint2) * (size_t)block;
 }
@@ -311,42 +316,74 @@ PT_DEV constexpr size_t trav_stack_lds_bytes(int lds, int block) {
 template <int LDS, bool COUNT = false>
 struct TravStack {
     static_assert(LDS >= 3, "push3 needs at least three LDS entries");
-    lds_uint2* lds;  // (reference, entry distance bits), one 64-bit LDS access per push / pop
-    uint2* gbl;      // spill area of all lanes (uniform); this lane's entry LDS + k is gbl[glane + k * gstride]
+#if !defined(__HIP_DEVICE_COMPILE__)
+    char* mem;  // this lane's entries
+#endif
+    uint32_t base;  // the wave's first entry row (LDS byte address, wave-uniform)
+    uint32_t top;   // this lane's next free entry (LDS byte address)
+    uint2* gbl;     // spill area of all lanes (uniform); this lane's entry LDS + k is gbl[glane + k * gstride]
     uint32_t glane;
-    int lstride;
     int gstride;
     int gcap;
-    int sp;
-    bool overflow;
+    uint32_t overflow;  // 1 once an entry did not fit (a number: a flag would live in mask registers and be merged at every branch)
     uint32_t nodes, tris;  // node visits and triangle tests of this lane (counted when COUNT)
+
+    PT_DEV uint2 get(uint32_t at) const {
+#if defined(__HIP_DEVICE_COMPILE__)
+        return lds_entry(at);
+#else
+        uint2 e;
+        memcpy(&e, mem + (at - base), sizeof e);
+        return e;
+#endif
+    }
+    PT_DEV void set(uint32_t at, uint2 e) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        lds_entry_set(at, e);
+#else
+        memcpy(mem + (at - base), &e, sizeof e);
+#endif
+    }
+    PT_DEV uint32_t bottom() const {
+#if defined(__HIP_DEVICE_COMPILE__)
+        return base + 8u * __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+#else
+        return base;
+#endif
+    }
+    PT_DEV void clear() { top = bottom(); }
+    PT_DEV bool empty() const { return top < base + kStackRow; }
 
     PT_DEV void push(uint32_t ref, float t) {
         const uint2 e = make_uint2(ref, f2u(t));
-        if (sp < LDS) {
-            lds[mul24((uint32_t)sp, (uint32_t)lstride)] = e;
-        } else if (sp - LDS < gcap) {
-            gbl[glane + (size_t)(sp - LDS) * (uint32_t)gstride] = e;
+        if (top < base + (uint32_t)LDS * kStackRow) {
+            set(top, e);
         } else {
-            overflow = true;
-            return;
+            const int k = (int)((top - base) / kStackRow) - LDS;
+            if (k < gcap) {
+                gbl[glane + (size_t)k * (uint32_t)gstride] = e;
+            } else {
+                overflow = 1u;
+                return;
+            }
         }
-        ++sp;
+        top += kStackRow;
     }
     // push e0, e1, e2 in this order, each only where its flag is set
     PT_DEV void push3(uint2 e0, bool v0, uint2 e1, bool v1, uint2 e2, bool v2) {
-        if (wave_none(sp > LDS - 3)) {
-            uint32_t s = (uint32_t)sp;
-            const uint32_t a0 = v0 ? s : (uint32_t)LDS;
-            s += v0 ? 1u : 0u;
-            const uint32_t a1 = v1 ? s : (uint32_t)LDS;
-            s += v1 ? 1u : 0u;
-            const uint32_t a2 = v2 ? s : (uint32_t)LDS;
-            s += v2 ? 1u : 0u;
-            lds[mul24(a0, (uint32_t)lstride)] = e0;
-            lds[mul24(a1, (uint32_t)lstride)] = e1;
-            lds[mul24(a2, (uint32_t)lstride)] = e2;
-            sp = (int)s;
+        if (wave_none(top >= base + (uint32_t)(LDS - 2) * kStackRow)) {
+            if (v0) {
+                set(top, e0);
+                top += kStackRow;
+            }
+            if (v1) {
+                set(top, e1);
+                top += kStackRow;
+            }
+            if (v2) {
+                set(top, e2);
+                top += kStackRow;
+            }
         } else {
             if (v0) push(e0.x, u2f(e0.y));
             if (v1) push(e1.x, u2f(e1.y));
@@ -354,17 +391,18 @@ struct TravStack {
         }
     }
     PT_DEV void pop(uint32_t& ref, float& t) {
-        --sp;
+        top -= kStackRow;
         uint2 e;
-        if (wave_none(sp >= LDS)) {
-            e = lds[mul24((uint32_t)sp, (uint32_t)lstride)];
-        } else if (sp < LDS) {
-            e = lds[mul24((uint32_t)sp, (uint32_t)lstride)];
+        if (wave_none(top >= base + (uint32_t)LDS * kStackRow)) {
+            e = get(top);
+        } else if (top < base + (uint32_t)LDS * kStackRow) {
+            e = get(top);
         } else {
             // a distinct load kind keeps the compiler from merging the two
             // branches into one flat load through a selected pointer
+            const uint32_t k = (top - base) / kStackRow - (uint32_t)LDS;
             const uint64_t g = __builtin_nontemporal_load(
-                reinterpret_cast<const uint64_t*>(gbl + glane + (size_t)(sp - LDS) * (uint32_t)gstride));
+                reinterpret_cast<const uint64_t*>(gbl + glane + (size_t)k * (uint32_t)gstride));
             e = make_uint2((uint32_t)g, (uint32_t)(g >> 32));
         }
         ref = e.x;
@@ -372,21 +410,26 @@ struct TravStack {
     }
 };
 
-// lds_lane: this lane's first LDS entry (entry k at lds_lane[k * lstride],
-// k = 0 .. LDS, the last one the discard slot);
+// lds: the block's stack memory (device) or this lane's entries (host: one
+// lane, LDS + 1 entries);
 // gbl: the spill area, where this lane's entry LDS + k is gbl[glane + k * gstride]
 template <int LDS, bool COUNT = false>
-PT_DEV TravStack<LDS, COUNT> make_trav_stack(uint2* lds_lane, int lstride, uint2* gbl, uint32_t glane, int gstride,
+PT_DEV TravStack<LDS, COUNT> make_trav_stack(uint2* lds, int /*lstride*/, uint2* gbl, uint32_t glane, int gstride,
                                              int gcap) {
     TravStack<LDS, COUNT> st;
-    st.lds = (lds_uint2*)lds_lane;
-    st.lstride = lstride;
+#if defined(__HIP_DEVICE_COMPILE__)
+    const uint32_t at = (uint32_t)reinterpret_cast<uintptr_t>((lds_uint2*)lds);
+    st.base = __builtin_amdgcn_readfirstlane(at + (threadIdx.x >> 6) * (uint32_t)(LDS + 1) * kStackRow);
+#else
+    st.mem = reinterpret_cast<char*>(lds);
+    st.base = 0u;
+#endif
     st.gbl = gbl;
     st.glane = glane;
     st.gstride = gstride;
     st.gcap = gcap;
-    st.sp = 0;
-    st.overflow = false;
+    st.clear();
+    st.overflow = 0u;
     st.nodes = st.tris = 0u;
     return st;
 }
@@ -425,8 +468,8 @@ PT_DEV float half_of(uint32_t w0, uint32_t w1, int c) {
 }
 
 // Conservative slab test of the four children of a node against (0, tlim]:
-// entry <= exit * (1 + 2^-16).  Writes the entry distances; returns a 4-bit
-// hit mask.
+// entry <= exit * (1 + 2^-16).  Writes the entry distances and which children
+// are hit.
 // A plane at o_a + h 2^e (o_a the node's origin, h a binary16 offset) is at
 // distance h (2^e inv_a) + (o_a inv_a - RN(o inv_a)): one fused
 // multiply-add per plane (the binary16 operand read in place) after three
@@ -438,10 +481,12 @@ PT_DEV float half_of(uint32_t w0, uint32_t w1, int c) {
 // box.  The encoding only widens the boxes (planes rounded outward).  Per
 // lane the near and far planes of an axis are chosen by the sign of its
 // inverse direction, so the entry and exit distances per axis need no
-// min/max.  Empty slots (planes +inf / -inf) are inverted boxes, also masked
-// out by their reference.  A NaN distance is ignored by fmaxf / fminf,
-// which keeps the test conservative.
-PT_DEV unsigned slab4_q(const Ray& r, const float4 q[5], float tlim, float tn[4]) {
+// min/max.  Empty slots (planes +inf / -inf) are inverted boxes; were one
+// accepted all the same (a direction whose scaled inverses vanish on every
+// axis), its reference, all ones, is out of range as a leaf and is skipped.
+// A NaN distance is ignored by fmaxf / fminf, which keeps the test
+// conservative.
+PT_DEV void slab4_q(const Ray& r, const float4 q[5], float tlim, float tn[4], bool hit[4]) {
     const uint32_t e = f2u(q[0].w);
     const float Ax = ldexpf(r.inv.x, (int)(e & 255u) - 128);
     const float Ay = ldexpf(r.inv.y, (int)((e >> 8) & 255u) - 128);
@@ -457,7 +502,6 @@ PT_DEV unsigned slab4_q(const Ray& r, const float4 q[5], float tlim, float tn[4]
     const uint32_t fy0 = f2u(sy ? q[2].x : q[2].z), fy1 = f2u(sy ? q[2].y : q[2].w);
     const uint32_t nz0 = f2u(sz ? q[3].z : q[3].x), nz1 = f2u(sz ? q[3].w : q[3].y);
     const uint32_t fz0 = f2u(sz ? q[3].x : q[3].z), fz1 = f2u(sz ? q[3].y : q[3].w);
-    unsigned mask = 0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         float ax = fmaf(half_of(nx0, nx1, c), Ax, Bx), bx = fmaf(half_of(fx0, fx1, c), Ax, Bx);
@@ -466,31 +510,38 @@ PT_DEV unsigned slab4_q(const Ray& r, const float4 q[5], float tlim, float tn[4]
         float t0 = fmaxf(fmaxf(ax, ay), fmaxf(az, 0.0f));
         float t1 = fminf(fminf(bx, by), fminf(bz, tlim));
         tn[c] = t0;
-        const float cref = c == 0 ? q[4].x : (c == 1 ? q[4].y : (c == 2 ? q[4].z : q[4].w));
-        if (t0 <= t1 * kBoxSlack && f2u(cref) != kEmptyRef) mask |= 1u << c;
+        hit[c] = t0 <= t1 * kBoxSlack;
     }
-    return mask;
 }
 
-
-// sort four (ref, t) pairs by t (ascending), invalid entries (t = +inf)
-// last; a select network, no branches
-PT_DEV void cswap(uint32_t& ra, float& ta, uint32_t& rb, float& tb) {
-    const bool s = tb < ta;
-    const float t0 = s ? tb : ta, t1 = s ? ta : tb;
-    const uint32_t r0 = s ? rb : ra, r1 = s ? ra : rb;
-    ta = t0;
-    tb = t1;
-    ra = r0;
-    rb = r1;
+// Entry (reference, distance) as one 64-bit word, the distance above: the
+// words of non-negative distances order as the distances do.  On the GPU
+// they are ordered as binary64 numbers (finite and positive for every
+// distance up to +inf and for kMissT), two full-rate instructions per
+// exchange where comparing distances and selecting both halves took five.
+constexpr uint32_t kMissT = 0x7FE00000u;  // a NaN distance: a child that is not hit, ordered after +inf
+PT_DEV uint2 entry_min(uint2 a, uint2 b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(__hiloint2double((int)a.y, (int)a.x)), "v"(__hiloint2double((int)b.y, (int)b.x)));
+    return make_uint2((uint32_t)__double2loint(r), (uint32_t)__double2hiint(r));
+#else
+    return (((uint64_t)a.y << 32) | a.x) < (((uint64_t)b.y << 32) | b.x) ? a : b;
+#endif
 }
-
-PT_DEV void sort4(uint32_t ref[4], float t[4]) {
-    cswap(ref[0], t[0], ref[1], t[1]);
-    cswap(ref[2], t[2], ref[3], t[3]);
-    cswap(ref[0], t[0], ref[2], t[2]);
-    cswap(ref[1], t[1], ref[3], t[3]);
-    cswap(ref[1], t[1], ref[2], t[2]);
+PT_DEV uint2 entry_max(uint2 a, uint2 b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(__hiloint2double((int)a.y, (int)a.x)), "v"(__hiloint2double((int)b.y, (int)b.x)));
+    return make_uint2((uint32_t)__double2loint(r), (uint32_t)__double2hiint(r));
+#else
+    return (((uint64_t)a.y << 32) | a.x) < (((uint64_t)b.y << 32) | b.x) ? b : a;
+#endif
+}
+PT_DEV void cswap(uint2& a, uint2& b) {
+    const uint2 lo = entry_min(a, b), hi = entry_max(a, b);
+    a = lo;
+    b = hi;
 }
 
 // One fetch per lane and traversal step: five float4 from the node (an
@@ -499,25 +550,85 @@ PT_DEV void sort4(uint32_t ref[4], float t[4]) {
 // the last record readable), issued by the same instructions for every
 // lane before any lane uses them.  A wave whose lanes are at inner nodes
 // and at leaves then waits for memory once per step, not once per branch.
-// `ok` = the reference is in range (else node 0 is read and ignored).
+// `ok` = the reference is in range (else node 0 is read and ignored).  The
+// record's offset is (i << s) + i, s = 1 for the three float4 of a triangle
+// and 2 for a node's five but four: no multiplication.
 PT_DEV void fetch_item(const SceneView& sc, uint32_t ref, bool ok, float4 q[5]) {
-    const uint32_t r = ok ? ref : 0u;
-    const float4* p = (r & kLeafBit) ? sc.tris + (size_t)(r & kLeafFirstMask) * 3 : sc.nodes + (size_t)mul24(r, 5u);
+    const uint32_t i = ok ? ref & kLeafFirstMask : 0u;
+    const bool tri = ok && (ref & kLeafBit) != 0;
+    const float4* p = (tri ? sc.tris : sc.nodes) + ((i << (tri ? 1u : 2u)) + i);
     q[0] = p[0];
     q[1] = p[1];
     q[2] = p[2];
     q[3] = p[3];
     q[4] = p[4];
+#if defined(__HIP_DEVICE_COMPILE__)
+    // keeps the compiler from moving the last load behind the leaf's code
+    asm volatile("" ::"v"(q[4].x), "v"(q[4].y), "v"(q[4].z), "v"(q[4].w));
+#endif
+}
+
+// the reference names nodes or triangles inside the arrays (`ref` a leaf or not)
+PT_DEV bool ref_ok(const SceneView& sc, uint32_t ref) {
+    const bool leaf = (ref & kLeafBit) != 0;
+    const uint32_t last = leaf ? (ref & kLeafFirstMask) + ((ref >> kLeafCountShift) & 15u) : ref;
+    return last < (uint32_t)(leaf ? sc.nt : sc.n_nodes);
+}
+
+// Inner node q of a closest-hit traversal (hits beyond tlim do not count):
+// descend into the nearest hit child and push the others, farthest first.
+// `ref` is left alone when no child is hit.
+template <int LDS, bool COUNT>
+PT_DEV void node_closest(const Ray& r, const float4 q[5], float tlim, uint32_t& ref, TravStack<LDS, COUNT>& st) {
+    float tn[4];
+    bool hit[4];
+    slab4_q(r, q, tlim, tn, hit);
+    uint2 e0 = make_uint2(f2u(q[4].x), hit[0] ? f2u(tn[0]) : kMissT), e1 = make_uint2(f2u(q[4].y), hit[1] ? f2u(tn[1]) : kMissT);
+    uint2 e2 = make_uint2(f2u(q[4].z), hit[2] ? f2u(tn[2]) : kMissT), e3 = make_uint2(f2u(q[4].w), hit[3] ? f2u(tn[3]) : kMissT);
+    cswap(e0, e1);
+    cswap(e2, e3);
+    cswap(e0, e2);
+    cswap(e1, e3);
+    cswap(e1, e2);
+    st.push3(e3, u2f(e3.y) <= INFINITY, e2, u2f(e2.y) <= INFINITY, e1, u2f(e1.y) <= INFINITY);
+    ref = u2f(e0.y) <= INFINITY ? e0.x : ref;
+}
+
+// Inner node of an any-hit traversal: descend into the last hit child, push
+// the other hit ones.  `ref` is left alone when no child is hit.
+template <int LDS, bool COUNT>
+PT_DEV void node_any(const Ray& r, const float4 q[5], float tlim, uint32_t& ref, TravStack<LDS, COUNT>& st) {
+    float tn[4];
+    bool h[4];
+    slab4_q(r, q, tlim, tn, h);
+    const uint32_t c0 = f2u(q[4].x), c1 = f2u(q[4].y), c2 = f2u(q[4].z), c3 = f2u(q[4].w);
+    const bool h23 = h[2] | h[3], h123 = h[1] | h23;
+    st.push3(make_uint2(c0, 0u), h[0] & h123, make_uint2(c1, 0u), h[1] & h23, make_uint2(c2, 0u), h[2] & h[3]);
+    ref = h[3] ? c3 : (h[2] ? c2 : (h[1] ? c1 : (h[0] ? c0 : ref)));
 }
 
 // Closest hit in (0, tmax): smallest t, ties to the smaller input id.
 // References outside the node or triangle arrays are skipped, so a damaged
 // BVH cannot make a lane read out of bounds.
 //
+// Bound by vector issue (a step ran about 310 vector instructions and as many
+// scalar ones, four cycles each and eight for a wave alone on its SIMD) and
+// by the vector cache (five 16-byte loads of 64 records far apart: 207 cycles
+// of a compute unit from L1, 275 from L2).  Hence the number of instructions
+// decides, also for a frame too small to fill the GPU: entries ordered as
+// 64-bit words, a stack pointer that is an address, state in registers
+// instead of flags, no multiplications.  The 1.02M-triangle 1080p frame:
+// wavefront 2.41 -> 2.16 ms, megakernel 3.31 -> 2.85; eight frames in flight
+// 13.7 -> 12.1; the two-level scene 9.33 -> 8.88.
+//
 // The traversal is written as a resumable step (closest_step), so that a
 // persistent kernel can run one step per loop trip and hand a finished
 // lane a new ray while the others are still traversing.  closest_hit runs
 // the steps to the end.
+//
+// kDoneRef: no next reference.  As a leaf it would start beyond any
+// triangle array (at most 2^27 triangles), so no scene holds it.
+constexpr uint32_t kDoneRef = 0xFFFFFFFDu;
 
 template <int LDS, bool COUNT = false>
 PT_DEV void closest_begin(float tmax, Hit& h, uint32_t& ref, TravStack<LDS, COUNT>& st) {
@@ -527,76 +638,78 @@ PT_DEV void closest_begin(float tmax, Hit& h, uint32_t& ref, TravStack<LDS, COUN
     h.det = 1.0f;
     h.tri = 0xFFFFFFFFu;
     h.id = 0xFFFFFFFFu;
-    st.sp = 0;
+    st.clear();
     ref = 0;  // root
+}
+
+// One triangle record (a, b, c) at leaf-order index i: the closest hit so far
+PT_DEV void tri_closest(const Ray& r, float tmax, uint32_t i, float4 a, float4 b, float4 c, Hit& h) {
+    float t, vn, wn, dn;
+    if (tri_test(r, xyz(a), xyz(b), xyz(c), t, vn, wn, dn)) {
+        const uint32_t id = f2u(a.w);
+        if ((t < tmax) & ((t < h.t) | ((t == h.t) & (id < h.id)))) {
+            h.t = t;
+            h.b1 = vn;
+            h.b2 = wn;
+            h.det = dn;
+            h.tri = i;
+            h.id = id;
+        }
+    }
+}
+
+// The triangles [first, first + cnt) of a leaf, the first one's record in q
+template <int LDS, bool COUNT>
+PT_DEV void leaf_closest(const SceneView& sc, const Ray& r, float tmax, uint32_t first, uint32_t cnt, const float4 q[5],
+                         Hit& h, TravStack<LDS, COUNT>& st) {
+    if constexpr (COUNT) st.tris += cnt;
+    tri_closest(r, tmax, first, q[0], q[1], q[2], h);
+    for (uint32_t i = first + 1u; i < first + cnt; ++i) {
+        const float4* tp = sc.tris + (size_t)i * 3;
+        tri_closest(r, tmax, i, tp[0], tp[1], tp[2], h);
+    }
+}
+
+// True when a triangle of the leaf is hit
+template <int LDS, bool COUNT>
+PT_DEV bool leaf_any(const SceneView& sc, const Ray& r, float tmax, uint32_t first, uint32_t cnt, const float4 q[5],
+                     TravStack<LDS, COUNT>& st) {
+    if constexpr (COUNT) ++st.tris;
+    float t, vn, wn, dn;
+    bool hit = tri_test(r, xyz(q[0]), xyz(q[1]), xyz(q[2]), t, vn, wn, dn) & (t < tmax);
+    for (uint32_t i = first + 1u; i < first + cnt && !hit; ++i) {
+        if constexpr (COUNT) ++st.tris;
+        const float4* tp = sc.tris + (size_t)i * 3;
+        hit = tri_test(r, xyz(tp[0]), xyz(tp[1]), xyz(tp[2]), t, vn, wn, dn) & (t < tmax);
+    }
+    return hit;
 }
 
 // Visit `ref` (an inner node: push the farther hit children, move to the
 // nearest; a leaf: test its triangles), then pop the next entry that can
-// still hold a closer hit.  Returns false when the traversal is finished.
+// still hold a closer hit.  `ref` becomes kDoneRef when the traversal is
+// finished: a number in a register, where a flag would be a mask that every
+// branch of the step has to merge.
 template <int LDS, bool COUNT = false>
-PT_DEV bool closest_step(const SceneView& sc, const Ray& r, float tmax, Hit& h, uint32_t& ref, TravStack<LDS, COUNT>& st) {
+PT_DEV void closest_step(const SceneView& sc, const Ray& r, float tmax, Hit& h, uint32_t& ref, TravStack<LDS, COUNT>& st) {
     const bool leaf = (ref & kLeafBit) != 0;
     const uint32_t first = ref & kLeafFirstMask;
     const uint32_t cnt = ((ref >> kLeafCountShift) & 15u) + 1u;
-    const bool ok = leaf ? first + cnt <= (uint32_t)sc.nt : ref < (uint32_t)sc.n_nodes;
+    const bool ok = ref_ok(sc, ref);
     float4 q[5];
     fetch_item(sc, ref, ok, q);
-    if (!leaf) {
-        if (ok) {
-            if constexpr (COUNT) ++st.nodes;
-            float tn[4];
-            unsigned m = slab4_q(r, q, h.t, tn);
-            if (m) {
-                uint32_t rr[4];
-                float tt[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    bool hit = (m >> c) & 1u;
-                    const float cref = c == 0 ? q[4].x : (c == 1 ? q[4].y : (c == 2 ? q[4].z : q[4].w));
-                    rr[c] = hit ? f2u(cref) : kEmptyRef;
-                    tt[c] = hit ? tn[c] : INFINITY;
-                }
-                sort4(rr, tt);
-                // push the farther hits (farthest first), descend into the nearest
-                st.push3(make_uint2(rr[3], f2u(tt[3])), rr[3] != kEmptyRef, make_uint2(rr[2], f2u(tt[2])),
-                         rr[2] != kEmptyRef, make_uint2(rr[1], f2u(tt[1])), rr[1] != kEmptyRef);
-                ref = rr[0];
-                return true;
-            }
-        }
-    } else {
-        if (ok) {
-            if constexpr (COUNT) st.tris += cnt;
-            for (uint32_t i = first; i < first + cnt; ++i) {
-                float4 a = q[0], b = q[1], c = q[2];  // the first triangle came with the fetch
-                if (i != first) {
-                    const float4* tp = sc.tris + (size_t)i * 3;
-                    a = tp[0];
-                    b = tp[1];
-                    c = tp[2];
-                }
-                float t, vn, wn, dn;
-                if (tri_test(r, xyz(a), xyz(b), xyz(c), t, vn, wn, dn) && t < tmax) {
-                    uint32_t id = f2u(a.w);
-                    if (t < h.t || (t == h.t && id < h.id)) {
-                        h.t = t;
-                        h.b1 = vn;
-                        h.b2 = wn;
-                        h.det = dn;
-                        h.tri = i;
-                        h.id = id;
-                    }
-                }
-            }
-        }
+    ref = kDoneRef;  // the next reference; none so far
+    if (!leaf & ok) {
+        if constexpr (COUNT) ++st.nodes;
+        node_closest(r, q, h.t, ref, st);
     }
-    while (st.sp > 0) {
+    if (leaf & ok) leaf_closest(sc, r, tmax, first, cnt, q, h, st);
+    while ((ref == kDoneRef) & !st.empty()) {
+        uint32_t next;
         float t;
-        st.pop(ref, t);
-        if (t <= h.t * kBoxSlack) return true;
+        st.pop(next, t);
+        if (t <= h.t * kBoxSlack) ref = next;
     }
-    return false;
 }
 
 template <int LDS, bool COUNT = false>
@@ -604,8 +717,7 @@ PT_DEV Hit closest_hit(const SceneView& sc, const Ray& r, float tmax, TravStack<
     Hit h;
     uint32_t ref;
     closest_begin<LDS>(tmax, h, ref, st);
-    while (closest_step<LDS>(sc, r, tmax, h, ref, st)) {
-    }
+    while (ref != kDoneRef) closest_step<LDS>(sc, r, tmax, h, ref, st);
     hit_finish(h);
     return h;
 }
@@ -627,71 +739,47 @@ PT_DEV void hit_barycentrics(const SceneView& sc, f3 o, f3 d, Hit& h) {
 }
 
 // Any hit in (0, tmax), as resumable steps: any_step visits `ref` and pops
-// the next entry; it returns false when the traversal is finished, with
+// the next entry; `ref` becomes kDoneRef when the traversal is finished, with
 // `occluded` set if a triangle was hit.
 template <int LDS, bool COUNT = false>
 PT_DEV void any_begin(uint32_t& ref, TravStack<LDS, COUNT>& st) {
-    st.sp = 0;
+    st.clear();
     ref = 0;
 }
 
 template <int LDS, bool COUNT = false>
-PT_DEV bool any_step(const SceneView& sc, const Ray& r, float tmax, uint32_t& ref, TravStack<LDS, COUNT>& st,
-                     bool& occluded) {
+PT_DEV void any_step(const SceneView& sc, const Ray& r, float tmax, uint32_t& ref, TravStack<LDS, COUNT>& st,
+                     uint32_t& occluded) {
     const bool leaf = (ref & kLeafBit) != 0;
     const uint32_t first = ref & kLeafFirstMask;
     const uint32_t cnt = ((ref >> kLeafCountShift) & 15u) + 1u;
-    const bool ok = leaf ? first + cnt <= (uint32_t)sc.nt : ref < (uint32_t)sc.n_nodes;
+    const bool ok = ref_ok(sc, ref);
     float4 q[5];
     fetch_item(sc, ref, ok, q);
-    if (!leaf) {
-        if (ok) {
-            if constexpr (COUNT) ++st.nodes;
-            float tn[4];
-            unsigned m = slab4_q(r, q, tmax, tn);
-            if (m) {
-                // descend into the last hit child, push the other hit ones
-                const uint32_t cr[4] = {f2u(q[4].x), f2u(q[4].y), f2u(q[4].z), f2u(q[4].w)};
-                const uint32_t last = 31u - (uint32_t)__builtin_clz(m);
-                st.push3(make_uint2(cr[0], f2u(tn[0])), (m & 1u) && last > 0u, make_uint2(cr[1], f2u(tn[1])),
-                         ((m >> 1) & 1u) && last > 1u, make_uint2(cr[2], f2u(tn[2])), ((m >> 2) & 1u) && last > 2u);
-                ref = last == 0u ? cr[0] : (last == 1u ? cr[1] : (last == 2u ? cr[2] : cr[3]));
-                return true;
-            }
-        }
-    } else {
-        if (ok) {
-            for (uint32_t i = first; i < first + cnt; ++i) {
-                if constexpr (COUNT) ++st.tris;
-                float4 a = q[0], b = q[1], c = q[2];  // the first triangle came with the fetch
-                if (i != first) {
-                    const float4* tp = sc.tris + (size_t)i * 3;
-                    a = tp[0];
-                    b = tp[1];
-                    c = tp[2];
-                }
-                float t, vn, wn, dn;
-                if (tri_test(r, xyz(a), xyz(b), xyz(c), t, vn, wn, dn) && t < tmax) {
-                    occluded = true;
-                    return false;
-                }
-            }
+    ref = kDoneRef;
+    if (!leaf & ok) {
+        if constexpr (COUNT) ++st.nodes;
+        node_any(r, q, tmax, ref, st);
+    }
+    if (leaf & ok) {
+        if (leaf_any(sc, r, tmax, first, cnt, q, st)) {
+            occluded = 1u;
+            st.clear();
         }
     }
-    if (st.sp == 0) return false;
-    float t;
-    st.pop(ref, t);
-    return true;
+    if ((ref == kDoneRef) & !st.empty()) {
+        float t;
+        st.pop(ref, t);
+    }
 }
 
 template <int LDS, bool COUNT = false>
 PT_DEV bool any_hit(const SceneView& sc, const Ray& r, float tmax, TravStack<LDS, COUNT>& st) {
     uint32_t ref;
     any_begin<LDS>(ref, st);
-    bool occluded = false;
-    while (any_step<LDS>(sc, r, tmax, ref, st, occluded)) {
-    }
-    return occluded;
+    uint32_t occluded = 0u;
+    while (ref != kDoneRef) any_step<LDS>(sc, r, tmax, ref, st, occluded);
+    return occluded != 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -731,13 +819,13 @@ PT_DEV void inst_begin(f3 o, f3 d, InstTrav& it) {
     it.obj = false;
 }
 
-// Enter the instance of top-level leaf `ref`: object-space ray, marker, the
-// mesh's root as the next reference.  False for a reference outside the
+// Enter the instance of top-level leaf `at`: object-space ray, marker, the
+// mesh's root as the next reference.  Nothing for a leaf outside the
 // instance records.
 template <int LDS, bool COUNT>
-PT_DEV bool inst_enter(const SceneView& sc, Ray& r, InstTrav& it, uint32_t& ref, TravStack<LDS, COUNT>& st) {
-    const uint32_t rec = ref & kLeafFirstMask;
-    if (rec >= (uint32_t)sc.n_inst) return false;
+PT_DEV void inst_enter(const SceneView& sc, Ray& r, InstTrav& it, uint32_t at, uint32_t& ref, TravStack<LDS, COUNT>& st) {
+    const uint32_t rec = at & kLeafFirstMask;
+    if (rec >= (uint32_t)sc.n_inst) return;
     const float4* ip = sc.insts + (size_t)rec * kInstRecord;
     const float4 w0 = ip[0], w1 = ip[1], w2 = ip[2], meta = ip[6];
     r = make_ray(xform_point(w0, w1, w2, it.o), xform_dir(w0, w1, w2, it.d));
@@ -746,89 +834,71 @@ PT_DEV bool inst_enter(const SceneView& sc, Ray& r, InstTrav& it, uint32_t& ref,
     it.iid = f2u(meta.y);
     st.push(kInstMarker, 0.0f);
     ref = f2u(meta.x);
-    return true;
 }
 
-// closest_step over a two-level scene; closest-hit key (t, input instance,
+// tri_closest inside the instance `it`; closest-hit key (t, input instance,
 // input triangle)
+PT_DEV void tri_closest_inst(const Ray& r, const InstTrav& it, float tmax, uint32_t i, float4 a, float4 b, float4 c,
+                             Hit& h) {
+    float t, vn, wn, dn;
+    if (tri_test(r, xyz(a), xyz(b), xyz(c), t, vn, wn, dn)) {
+        const uint32_t id = f2u(a.w);
+        if ((t < tmax) & ((t < h.t) | ((t == h.t) & ((it.iid < h.iid) | ((it.iid == h.iid) & (id < h.id)))))) {
+            h.t = t;
+            h.b1 = vn;
+            h.b2 = wn;
+            h.det = dn;
+            h.tri = i;
+            h.id = id;
+            h.inst = it.rec;
+            h.iid = it.iid;
+        }
+    }
+}
+
+// closest_step over a two-level scene
 template <int LDS, bool COUNT = false, bool SPLIT = false>
-PT_DEV bool closest_step_inst(const SceneView& sc, Ray& r, InstTrav& it, float tmax, Hit& h, uint32_t& ref,
+PT_DEV void closest_step_inst(const SceneView& sc, Ray& r, InstTrav& it, float tmax, Hit& h, uint32_t& ref,
                               TravStack<LDS, COUNT>& st) {
     // one fetch as in closest_step (an instance leaf fetches its record in
     // inst_enter instead); SPLIT: each branch fetches its own (the
     // megakernel's two-level traversal, whose register budget the single
     // fetch exceeds)
-    const bool leaf = (ref & kLeafBit) != 0;
-    const uint32_t first = ref & kLeafFirstMask;
-    const uint32_t cnt = ((ref >> kLeafCountShift) & 15u) + 1u;
-    const bool ok = leaf ? it.obj && first + cnt <= (uint32_t)sc.nt : ref < (uint32_t)sc.n_nodes;
+    const uint32_t at = ref;
+    const bool leaf = (at & kLeafBit) != 0;
+    const uint32_t first = at & kLeafFirstMask;
+    const uint32_t cnt = ((at >> kLeafCountShift) & 15u) + 1u;
+    const bool ok = ref_ok(sc, at) & (!leaf | it.obj);
     float4 q[5];
-    if constexpr (!SPLIT) fetch_item(sc, ref, ok, q);
-    if (!leaf) {
-        if (ok) {
-            if constexpr (SPLIT) fetch_item(sc, ref, true, q);
-            if constexpr (COUNT) ++st.nodes;
-            float tn[4];
-            unsigned m = slab4_q(r, q, h.t, tn);
-            if (m) {
-                uint32_t rr[4];
-                float tt[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    bool hit = (m >> c) & 1u;
-                    const float cref = c == 0 ? q[4].x : (c == 1 ? q[4].y : (c == 2 ? q[4].z : q[4].w));
-                    rr[c] = hit ? f2u(cref) : kEmptyRef;
-                    tt[c] = hit ? tn[c] : INFINITY;
-                }
-                sort4(rr, tt);
-                st.push3(make_uint2(rr[3], f2u(tt[3])), rr[3] != kEmptyRef, make_uint2(rr[2], f2u(tt[2])),
-                         rr[2] != kEmptyRef, make_uint2(rr[1], f2u(tt[1])), rr[1] != kEmptyRef);
-                ref = rr[0];
-                return true;
-            }
-        }
-    } else if (!it.obj) {
-        if (inst_enter<LDS, COUNT>(sc, r, it, ref, st)) return true;
-    } else {
-        if (ok) {
-            if constexpr (SPLIT) fetch_item(sc, ref, true, q);
-            if constexpr (COUNT) st.tris += cnt;
-            for (uint32_t i = first; i < first + cnt; ++i) {
-                float4 a = q[0], b = q[1], c = q[2];  // the first triangle came with the fetch
-                if (i != first) {
-                    const float4* tp = sc.tris + (size_t)i * 3;
-                    a = tp[0];
-                    b = tp[1];
-                    c = tp[2];
-                }
-                float t, vn, wn, dn;
-                if (tri_test(r, xyz(a), xyz(b), xyz(c), t, vn, wn, dn) && t < tmax) {
-                    uint32_t id = f2u(a.w);
-                    if (t < h.t || (t == h.t && (it.iid < h.iid || (it.iid == h.iid && id < h.id)))) {
-                        h.t = t;
-                        h.b1 = vn;
-                        h.b2 = wn;
-                        h.det = dn;
-                        h.tri = i;
-                        h.id = id;
-                        h.inst = it.rec;
-                        h.iid = it.iid;
-                    }
-                }
-            }
+    if constexpr (!SPLIT) fetch_item(sc, at, ok, q);
+    ref = kDoneRef;
+    if (!leaf & ok) {
+        if constexpr (SPLIT) fetch_item(sc, at, true, q);
+        if constexpr (COUNT) ++st.nodes;
+        node_closest(r, q, h.t, ref, st);
+    }
+    if (leaf & !it.obj) {
+        inst_enter<LDS, COUNT>(sc, r, it, at, ref, st);
+    } else if (leaf & ok) {
+        if constexpr (SPLIT) fetch_item(sc, at, true, q);
+        if constexpr (COUNT) st.tris += cnt;
+        tri_closest_inst(r, it, tmax, first, q[0], q[1], q[2], h);
+        for (uint32_t i = first + 1u; i < first + cnt; ++i) {
+            const float4* tp = sc.tris + (size_t)i * 3;
+            tri_closest_inst(r, it, tmax, i, tp[0], tp[1], tp[2], h);
         }
     }
-    while (st.sp > 0) {
+    while ((ref == kDoneRef) & !st.empty()) {
+        uint32_t next;
         float t;
-        st.pop(ref, t);
-        if (ref == kInstMarker) {
+        st.pop(next, t);
+        if (next == kInstMarker) {
             r = make_ray(it.o, it.d);
             it.obj = false;
-            continue;
+        } else if (t <= h.t * kBoxSlack) {
+            ref = next;
         }
-        if (t <= h.t * kBoxSlack) return true;
     }
-    return false;
 }
 
 template <int LDS, bool COUNT = false>
@@ -843,62 +913,41 @@ PT_DEV void closest_begin_inst(f3 o, f3 d, float tmax, Ray& r, InstTrav& it, Hit
 
 // any_step over a two-level scene
 template <int LDS, bool COUNT = false, bool SPLIT = false>
-PT_DEV bool any_step_inst(const SceneView& sc, Ray& r, InstTrav& it, float tmax, uint32_t& ref,
-                          TravStack<LDS, COUNT>& st, bool& occluded) {
-    const bool leaf = (ref & kLeafBit) != 0;
-    const uint32_t first = ref & kLeafFirstMask;
-    const uint32_t cnt = ((ref >> kLeafCountShift) & 15u) + 1u;
-    const bool ok = leaf ? it.obj && first + cnt <= (uint32_t)sc.nt : ref < (uint32_t)sc.n_nodes;
+PT_DEV void any_step_inst(const SceneView& sc, Ray& r, InstTrav& it, float tmax, uint32_t& ref,
+                          TravStack<LDS, COUNT>& st, uint32_t& occluded) {
+    const uint32_t at = ref;
+    const bool leaf = (at & kLeafBit) != 0;
+    const uint32_t first = at & kLeafFirstMask;
+    const uint32_t cnt = ((at >> kLeafCountShift) & 15u) + 1u;
+    const bool ok = ref_ok(sc, at) & (!leaf | it.obj);
     float4 q[5];
-    if constexpr (!SPLIT) fetch_item(sc, ref, ok, q);
-    if (!leaf) {
-        if (ok) {
-            if constexpr (SPLIT) fetch_item(sc, ref, true, q);
-            if constexpr (COUNT) ++st.nodes;
-            float tn[4];
-            unsigned m = slab4_q(r, q, tmax, tn);
-            if (m) {
-                const uint32_t cr[4] = {f2u(q[4].x), f2u(q[4].y), f2u(q[4].z), f2u(q[4].w)};
-                const uint32_t last = 31u - (uint32_t)__builtin_clz(m);
-                st.push3(make_uint2(cr[0], f2u(tn[0])), (m & 1u) && last > 0u, make_uint2(cr[1], f2u(tn[1])),
-                         ((m >> 1) & 1u) && last > 1u, make_uint2(cr[2], f2u(tn[2])), ((m >> 2) & 1u) && last > 2u);
-                ref = last == 0u ? cr[0] : (last == 1u ? cr[1] : (last == 2u ? cr[2] : cr[3]));
-                return true;
-            }
-        }
-    } else if (!it.obj) {
-        if (inst_enter<LDS, COUNT>(sc, r, it, ref, st)) return true;
-    } else {
-        if (ok) {
-            if constexpr (SPLIT) fetch_item(sc, ref, true, q);
-            for (uint32_t i = first; i < first + cnt; ++i) {
-                if constexpr (COUNT) ++st.tris;
-                float4 a = q[0], b = q[1], c = q[2];  // the first triangle came with the fetch
-                if (i != first) {
-                    const float4* tp = sc.tris + (size_t)i * 3;
-                    a = tp[0];
-                    b = tp[1];
-                    c = tp[2];
-                }
-                float t, vn, wn, dn;
-                if (tri_test(r, xyz(a), xyz(b), xyz(c), t, vn, wn, dn) && t < tmax) {
-                    occluded = true;
-                    return false;
-                }
-            }
+    if constexpr (!SPLIT) fetch_item(sc, at, ok, q);
+    ref = kDoneRef;
+    if (!leaf & ok) {
+        if constexpr (SPLIT) fetch_item(sc, at, true, q);
+        if constexpr (COUNT) ++st.nodes;
+        node_any(r, q, tmax, ref, st);
+    }
+    if (leaf & !it.obj) {
+        inst_enter<LDS, COUNT>(sc, r, it, at, ref, st);
+    } else if (leaf & ok) {
+        if constexpr (SPLIT) fetch_item(sc, at, true, q);
+        if (leaf_any(sc, r, tmax, first, cnt, q, st)) {
+            occluded = 1u;
+            st.clear();
         }
     }
-    while (st.sp > 0) {
+    while ((ref == kDoneRef) & !st.empty()) {
+        uint32_t next;
         float t;
-        st.pop(ref, t);
-        if (ref == kInstMarker) {
+        st.pop(next, t);
+        if (next == kInstMarker) {
             r = make_ray(it.o, it.d);
             it.obj = false;
-            continue;
+        } else {
+            ref = next;
         }
-        return true;
     }
-    return false;
 }
 
 // Closest hit and any hit in (0, tmax) of the world ray (o, d): the flat
@@ -911,8 +960,7 @@ PT_DEV Hit closest_hit_t(const SceneView& sc, f3 o, f3 d, float tmax, TravStack<
         InstTrav it;
         uint32_t ref;
         closest_begin_inst<LDS>(o, d, tmax, r, it, h, ref, st);
-        while (closest_step_inst<LDS, COUNT, true>(sc, r, it, tmax, h, ref, st)) {
-        }
+        while (ref != kDoneRef) closest_step_inst<LDS, COUNT, true>(sc, r, it, tmax, h, ref, st);
         hit_finish(h);
         return h;
     } else {
@@ -927,10 +975,9 @@ PT_DEV bool any_hit_t(const SceneView& sc, f3 o, f3 d, float tmax, TravStack<LDS
         inst_begin(o, d, it);
         uint32_t ref;
         any_begin<LDS>(ref, st);
-        bool occluded = false;
-        while (any_step_inst<LDS, COUNT, true>(sc, r, it, tmax, ref, st, occluded)) {
-        }
-        return occluded;
+        uint32_t occluded = 0u;
+        while (ref != kDoneRef) any_step_inst<LDS, COUNT, true>(sc, r, it, tmax, ref, st, occluded);
+        return occluded != 0u;
     } else {
         return any_hit<LDS>(sc, make_ray(o, d), tmax, st);
     }

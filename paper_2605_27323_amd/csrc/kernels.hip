@@ -12,7 +12,7 @@ namespace {
 template <int LDS, bool COUNT>
 __device__ __forceinline__ TravStack<LDS, COUNT> make_stack(uint32_t* smem, uint2* ovf, int gcap, uint32_t gtid,
                                                             uint32_t nlanes) {
-    return make_trav_stack<LDS, COUNT>(reinterpret_cast<uint2*>(smem) + threadIdx.x, (int)blockDim.x, ovf, gtid,
+    return make_trav_stack<LDS, COUNT>(reinterpret_cast<uint2*>(smem), (int)blockDim.x, ovf, gtid,
                                        (int)nlanes, gcap);
 }
 
@@ -246,31 +246,33 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
     const uint32_t nlanes = gridDim.x * blockDim.x;
     const uint32_t gtid = blockIdx.x * blockDim.x + threadIdx.x;
     TravStack<LDS, COUNT> st = make_stack<LDS, COUNT>(smem, ovf, gcap, gtid, nlanes);
-    const int cur = b & 1;
+    const float4 *__restrict__ ray_o = wb.ray_o[b & 1], *__restrict__ ray_d = wb.ray_d[b & 1];
     // with a ray sort this bounce, position i of the queue is slot perm[i]
     const uint32_t* perm = (sorted && wb.hist[2 * kSortBins]) ? wb.perm : nullptr;
     __shared__ uint32_t cursor;
     const BlockShare share = open_share(wb.counts[live_slot(wb, b)], wb.simds, &cursor, xcd_local);
     bool more = share.at(0u) < share.hi;  // the share holds further entries (wave-uniform)
     uint32_t want = share.start;          // entries to take next at most
-    bool live = false;
-    uint32_t item = 0, ref = 0;
+    uint32_t item = 0, ref = kDoneRef;  // a lane without a ray
+    float4* __restrict__ hits = wb.hit;
     Ray ray;
     Hit h;
     InstTrav it;
     while (true) {
-        const uint64_t idle = __ballot(!live);
+        const uint64_t idle = __ballot(ref == kDoneRef);
         const uint32_t nidle = (uint32_t)__popcll(idle);
         if (more && (nidle >= refill || nidle == 64u)) {
             const uint32_t n = min(nidle, want), c = share.take(n, more);
             want = 64u;
-            if (!live) {
+            if (ref == kDoneRef) {
                 const uint32_t r = rank_in(idle), pos = share.at(c + r);
                 if (r < n && pos < share.hi) {
                     const uint32_t i = perm ? perm[pos] : pos;
-                    // both loads issued before either is used (one wait)
-                    const float4 o4 = wb.ray_o[cur][i];
-                    const float4 d4 = wb.ray_d[cur][i];
+                    // both loads issued before either is used (one wait): the
+                    // empty asm keeps the second from moving behind the test
+                    const float4 o4 = ray_o[i];
+                    const float4 d4 = ray_d[i];
+                    asm volatile("" ::"v"(d4.x));
                     if (f2u(o4.w) != kDeadPath) {  // dead slots (no compaction) need no hit
                         if constexpr (INST) {
                             closest_begin_inst<LDS>(xyz(o4), xyz(d4), INFINITY, ray, it, h, ref, st);
@@ -279,25 +281,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
                             closest_begin<LDS>(INFINITY, h, ref, st);
                         }
                         item = i;
-                        live = true;
                     }
                 }
             }
-        }
-        if (__ballot(live) == 0ull) {
-            if (more) continue;
+        } else if (nidle == 64u) {
             break;
         }
-        if constexpr (INST) {
-            if (live && !closest_step_inst<LDS>(sc, ray, it, INFINITY, h, ref, st)) {
-                wb.hit[item] = make_float4(h.t, u2f(h.inst), 0.f, u2f(h.tri));
-                live = false;
-            }
-        } else {
-            if (live && !closest_step<LDS>(sc, ray, INFINITY, h, ref, st)) {
-                wb.hit[item] = make_float4(h.t, 0.f, 0.f, u2f(h.tri));
-                live = false;
-            }
+        if (ref != kDoneRef) {
+            if constexpr (INST) closest_step_inst<LDS>(sc, ray, it, INFINITY, h, ref, st);
+            else closest_step<LDS>(sc, ray, INFINITY, h, ref, st);
+            if (ref == kDoneRef) hits[item] = make_float4(h.t, INST ? u2f(h.inst) : 0.f, 0.f, u2f(h.tri));
         }
     }
     if constexpr (COUNT) {
@@ -366,38 +359,34 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
     const BlockShare share = open_share(wb.counts[wb.sh_base + b], wb.simds, &cursor, xcd_local);
     bool more = share.at(0u) < share.hi;  // the share holds further entries (wave-uniform)
     uint32_t want = share.start;          // entries to take next at most
-    bool live = false;
-    uint32_t item = 0, ref = 0;
+    const float4 *__restrict__ sh_o = wb.sh_o, *__restrict__ sh_d = wb.sh_d;
+    uint32_t item = 0, ref = kDoneRef;  // a lane without a ray
     Ray ray;
     InstTrav it;
+    uint32_t occluded = 0u;
     while (true) {
-        const uint64_t idle = __ballot(!live);
+        const uint64_t idle = __ballot(ref == kDoneRef);
         const uint32_t nidle = (uint32_t)__popcll(idle);
         if (more && (nidle >= refill || nidle == 64u)) {
             const uint32_t n = min(nidle, want), c = share.take(n, more);
             want = 64u;
-            if (!live) {
+            if (ref == kDoneRef) {
                 const uint32_t r = rank_in(idle), i = share.at(c + r);
                 if (r < n && i < share.hi) {
-                    ray = make_ray(xyz(wb.sh_o[i]), xyz(wb.sh_d[i]));
+                    ray = make_ray(xyz(sh_o[i]), xyz(sh_d[i]));
                     if constexpr (INST) inst_begin(ray.o, ray.d, it);
                     any_begin<LDS>(ref, st);
+                    occluded = 0u;
                     item = i;
-                    live = true;
                 }
             }
-        }
-        if (__ballot(live) == 0ull) {
-            if (more) continue;
+        } else if (nidle == 64u) {
             break;
         }
-        if (live) {
-            bool occluded = false;
-            bool more;
-            if constexpr (INST) more = any_step_inst<LDS>(sc, ray, it, kShadowTmax, ref, st, occluded);
-            else more = any_step<LDS>(sc, ray, kShadowTmax, ref, st, occluded);
-            if (!more) {
-                live = false;
+        if (ref != kDoneRef) {
+            if constexpr (INST) any_step_inst<LDS>(sc, ray, it, kShadowTmax, ref, st, occluded);
+            else any_step<LDS>(sc, ray, kShadowTmax, ref, st, occluded);
+            if (ref == kDoneRef) {
                 if (!occluded) shadow_add(wb, item);
                 shadow_record(wb, b, item, !occluded);
             }
