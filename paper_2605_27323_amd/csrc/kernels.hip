@@ -239,8 +239,15 @@ __global__ void __launch_bounds__(256) k_raygen(CamView cam, PathParams pp, Wave
 // time in use (543 us, ends from 48 to 543 us), with shares it has 70 % (360
 // us with the leaner step of device.h); the frame went from 2.61 to 2.41 ms,
 // a 65536-path frame of the Cornell room from 0.351 to 0.247 ms.
+// Waves per SIMD of the stage traversal kernels.  Flat scenes: eight (64
+// registers, none spilled; at seven or six the compiler's schedule was 4 %
+// slower).  Two-level scenes keep the world ray and the instance beside the
+// active ray: at eight waves 27 registers spilled in the loop, at five none
+// (the 4017-instance 1080p frame 8.83 -> 5.57 ms; four and six the same).
+constexpr int trav_waves(bool inst) { return inst ? 5 : 8; }
+
 template <int LDS, bool COUNT, bool INST>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k_extend(SceneView sc, WaveBufs wb, int b, uint2* __restrict__ ovf, int gcap,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trav_waves(INST)))) k_extend(SceneView sc, WaveBufs wb, int b, uint2* __restrict__ ovf, int gcap,
                                                 uint32_t refill, int sorted, int xcd_local) {
     extern __shared__ __align__(8) uint32_t smem[];
     const uint32_t nlanes = gridDim.x * blockDim.x;
@@ -349,7 +356,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 }
 
 template <int LDS, bool COUNT, bool INST>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k_shadow(SceneView sc, WaveBufs wb, int b, uint2* __restrict__ ovf, int gcap,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trav_waves(INST)))) k_shadow(SceneView sc, WaveBufs wb, int b, uint2* __restrict__ ovf, int gcap,
                                                 uint32_t refill, int xcd_local) {
     extern __shared__ __align__(8) uint32_t smem[];
     const uint32_t nlanes = gridDim.x * blockDim.x;
