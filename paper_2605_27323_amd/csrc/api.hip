@@ -115,6 +115,8 @@ struct pt_ctx {
     uint64_t last_npix = 0;
     bool last_acc = false;
     bool last_valid = false;
+    const uint32_t* last_rows = nullptr;  // a small frame: its workgroups' ray counts, else null
+    uint32_t last_nrows = 0;
 };
 
 namespace {
@@ -153,28 +155,64 @@ pt_status launch_config(const pt_ctx* c, const pt_render_args* a, Launch& L) {
 }
 
 struct WsLayout {
-    size_t counts, trav, ovf, ovf2, adj, rec_hit, rec_vis, wave[11], sort_key, perm, hist, total;
+    size_t counts, trav, ovf, ovf2, adj, rec_hit, rec_vis, wave[11], sort_key, perm, hist, rows, total;
     int ncounts;
+    uint32_t small_grid, small_per;  // a small frame's workgroups and paths per chunk (0: not a small frame)
 };
 constexpr int kTravWords = 16;  // 8 u64 traversal work counters
 
+// what a workspace is laid out for: a frame by itself, one of the frames in
+// flight, a backward; kStages: a frame that may not run as k_small
+enum class Use { kFrame, kInFlight, kBackward, kStages };
+
+// Whether the frame (or the backward's first replay) runs as k_small, and
+// how: one path per lane, `small_per` of them to a wave, whole pixels of an
+// image, so that every SIMD has one wave of paths.  An option that asks for
+// the stages themselves (their times, work counts, queues, sorts or
+// counters) keeps the stages.  The most paths it takes, by what it replaces:
+// us a frame of depth 8, stages against k_small, scenes of 1.02M triangles /
+// 94k triangles / a room of 352: 16000 paths 824 : 321, 433 : 117, 477 : 162;
+// 128000 paths 982 : 592, 528 : 174, 526 : 233; 259200 paths 1111 : 806, 571 :
+// 240, 565 : 317, but with a tuned hybrid tail 972 : 993 (and a backward 2220
+// : 2399); 512000 paths 1314 : 1459, 683 : 369, 659 : 566.  The megakernel
+// against it: 512000 paths 1468 : 1472, 619 : 374, 768 : 574; 1036800 paths 2144
+// : 2437, 692 : 558, 831 : 929.  Frames in flight, whose stages overlap, eight
+// frames: 64000 paths 2471 : 1965, 811 : 569; 120000 paths 2881 : 2995, 954 :
+// 842; 256000 paths 4839 : 6493, 1511 : 1752.
+void plan_small(const pt_ctx* c, const pt_render_args* a, Use use, WsLayout& w) {
+    if (use == Use::kStages || (a->flags & ~(PT_FLAG_XCD_LOCAL | PT_FLAG_KEEP_HITS | PT_FLAG_SERIAL_STAGES))) return;
+    const uint64_t npaths = (uint64_t)c->cam.W * c->cam.H * (uint64_t)a->spp;
+    const bool mega = a->mode == PT_MODE_MEGA, backward = use == Use::kBackward;
+    const uint64_t most = use == Use::kInFlight ? 1u << 16 : (mega ? 1u << 19 : 3u << 16);
+    if (npaths > most || a->max_depth > kSmallDepth) return;
+    if (backward ? mega : a->spp > 64) return;
+    const uint32_t simds = (uint32_t)c->num_cu * kSimdsPerCu, unit = backward ? 1u : (uint32_t)a->spp;
+    uint32_t per = std::min(64u, (uint32_t)((npaths + simds - 1) / simds));
+    per = std::max(unit, per / unit * unit);
+    w.small_per = per;
+    w.small_grid = (uint32_t)((npaths + per - 1) / per);
+}
+
 // workspace: counters | traversal overflow stack | adjoint path cursors and
 // radiance (backward only) | wavefront state (wavefront only)
-WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, bool backward = false) {
+WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use use = Use::kFrame) {
     WsLayout w{};
+    const bool backward = use == Use::kBackward;
     const size_t npaths = (size_t)c->cam.W * c->cam.H * a->spp;
     // [0, D+1] live paths per bounce, [D+2, 2D+2] shadow rays per bounce,
     // [2D+3, 2D+4] rays traced by the hybrid tail, [2D+6, 2D+7] the
     // two-slot count buffer (PT_FLAG_TWO_SLOT), the last word the overflow flag
     // (the megakernel's eight band cursors, u64, take words 8 .. 23)
     w.ncounts = std::max(2 * a->max_depth + 9, 24);
+    plan_small(c, a, use, w);
+    const size_t spill_lanes = std::max<size_t>(L.nlanes, (size_t)w.small_grid * kSmallBlock);
     size_t off = 0;
     w.counts = off;
     off = align_up(off + sizeof(uint32_t) * w.ncounts);
     w.trav = off;
     off = align_up(off + sizeof(uint32_t) * kTravWords);
     w.ovf = off;
-    off = align_up(off + sizeof(uint2) * (size_t)L.gcap * L.nlanes);
+    off = align_up(off + sizeof(uint2) * (size_t)L.gcap * spill_lanes);
     // the wavefront's shadow stage runs beside the next extend stage (on the
     // context's side stream) and spills its stacks to an area of its own
     const bool wave_mode = a->mode == PT_MODE_WAVE;
@@ -204,6 +242,8 @@ WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, bool 
     if (wave) off = align_up(off + sizeof(uint32_t) * npaths);
     w.hist = off;
     if (wave) off = align_up(off + sizeof(uint32_t) * (2 * kSortBins + 1));
+    w.rows = off;
+    if (w.small_grid) off = align_up(off + sizeof(uint32_t) * (size_t)small_row_words(a->max_depth) * w.small_grid);
     w.total = off;
     return w;
 }
@@ -270,6 +310,7 @@ void remember_frame(pt_ctx* c, const pt_render_args* a, uint32_t* counts, int nc
     c->last_sort_threshold = a->sort_threshold;
     c->last_npix = (uint64_t)c->cam.W * (uint64_t)c->cam.H;
     c->last_acc = acc;
+    c->last_rows = nullptr;
     c->last_valid = true;
 }
 
@@ -310,8 +351,30 @@ pt_status enqueue_stages(pt_ctx* c, const pt_render_args* a, const Launch& L, co
     dim3 grid(L.grid), block(L.block);
     const bool count = (a->flags & PT_FLAG_COUNT_WORK) != 0;
     const int xcd = (a->flags & PT_FLAG_XCD_LOCAL) ? 1 : 0;
-    PT_HIP(launch_init_counts(s, reinterpret_cast<uint32_t*>(trav), kTravWords, 0u), "init work counters");
     const uint32_t npaths = (uint32_t)c->cam.W * c->cam.H * a->spp;
+    if (w.small_grid) {
+        // the whole frame in one launch (a backward's path radiances go to
+        // the wavefront's buffer, its overflow flag to the stages' word)
+        uint32_t* rows = reinterpret_cast<uint32_t*>(base + w.rows);
+        float4* Lout = img ? nullptr : reinterpret_cast<float4*>(base + w.wave[10]);
+        WaveBufs wb{};
+        wb.L = Lout;
+        wb.simds = (uint32_t)c->num_cu * kSimdsPerCu;
+        if (rec) {
+            wb.rec_hit = rec->hit;
+            wb.rec_vis = rec->vis;
+            wb.rec_n = rec->npaths;
+        }
+        const SmallArgs sa{npaths, w.small_per, img, acc, rows, img ? nullptr : counts + (w.ncounts - 1)};
+        PT_HIP(launch_small(L.lds, w.small_grid, s, c->view, c->cam, pp, sa, wb, ovf, L.gcap), "small frame");
+        remember_frame(c, a, counts, w.ncounts, a->mode == PT_MODE_MEGA ? 0 : 1, acc != nullptr);
+        c->last_rows = rows;
+        c->last_nrows = w.small_grid;
+        c->last_trav = nullptr;
+        *Lbuf = Lout;
+        return PT_OK;
+    }
+    PT_HIP(launch_init_counts(s, reinterpret_cast<uint32_t*>(trav), kTravWords, 0u), "init work counters");
     if (a->mode == PT_MODE_MEGA) {
         PT_HIP(launch_init_counts(s, counts, w.ncounts, 0u), "init counters");
         // counters: [0] extension rays, [1] shadow rays, [2] overflow flag, [4..5] the
@@ -444,6 +507,38 @@ SceneView make_view(const pt_ctx* c, const pt_scene_buffers* b) {
     v.attrs = c->attr_leaf.empty() ? nullptr : reinterpret_cast<const float4*>(b->attributes);
     v.attr_flags = shading_flags(c);
     return v;
+}
+
+// The counters a small frame's schedule would have left, from the rays k_small
+// counted per bounce (see its rows): the megakernel's totals, or the
+// wavefront's counts per bounce up to the bounce the caller's hybrid tail
+// takes over and the tail's rays from there.
+pt_status small_counts(const pt_ctx* c, std::vector<uint32_t>& h) {
+    const int D = c->last_D;
+    const size_t nb = (size_t)D + 2, words = small_row_words(D);
+    std::vector<uint32_t> rows(words * c->last_nrows);
+    PT_HIP(hipMemcpy(rows.data(), c->last_rows, rows.size() * sizeof(uint32_t), hipMemcpyDeviceToHost), "read counters");
+    std::vector<uint32_t> sum(words, 0u);
+    for (size_t i = 0; i < rows.size(); ++i) sum[i % words] += rows[i];
+    const uint32_t *E = sum.data(), *S = E + nb;
+    if (c->last_kind == 0) {
+        for (size_t b = 0; b < nb; ++b) {
+            h[0] += E[b];
+            h[1] += S[b];
+        }
+        h[2] = sum[2 * nb] ? 1u : 0u;
+        return PT_OK;
+    }
+    bool in_tail = false;
+    for (int b = 0; b <= D; ++b) {
+        if (in_tail) h[2 * D + 3] += E[b];
+        else h[b] = E[b];
+        in_tail = in_tail || (c->last_tail && E[b] < c->last_tail) || (c->last_tail_bounce > 0 && b >= c->last_tail_bounce);
+        if (in_tail) h[2 * D + 4] += S[b];
+        else h[D + 2 + b] = S[b];
+    }
+    h[c->last_ncounts - 1] = sum[2 * nb] ? 1u : 0u;
+    return PT_OK;
 }
 
 }  // namespace
@@ -789,7 +884,7 @@ pt_status pt_backward_workspace_size(pt_ctx* c, const pt_render_args* a, uint64_
     Launch L;
     pt_status st = launch_config(c, a, L);
     if (st) return st;
-    *bytes = layout(c, a, L, true).total;
+    *bytes = layout(c, a, L, Use::kBackward).total;
     return PT_OK;
 }
 
@@ -812,13 +907,13 @@ pt_status pt_render_frame(pt_ctx* c, const pt_render_args* a, float* img, float*
     c->event_next = 0;
     const float4* Lbuf = nullptr;
     hipStream_t s2 = nullptr;
-    if (a->mode == PT_MODE_WAVE && !(a->flags & PT_FLAG_SERIAL_STAGES)) {
+    if (a->mode == PT_MODE_WAVE && !(a->flags & PT_FLAG_SERIAL_STAGES) && !w.small_grid) {
         st = side_stream(c, 2 * (a->max_depth + 1), s2);
         if (st) return st;
     }
     st = enqueue_stages(c, a, L, w, static_cast<char*>(ws), s, img, acc, prof, &Lbuf, nullptr, s2);
     if (st) return st;
-    if (a->mode == PT_MODE_WAVE) {
+    if (Lbuf) {
         PathParams pp{a->spp, a->max_depth, a->nee ? 1 : 0, a->rr_start, a->seed, a->frame, a->job, a->sampler};
         PT_HIP(timed(c, prof, 4, s, [&] { return launch_accumulate(dim3(L.grid), dim3(L.block), s, c->cam, pp, Lbuf, img, acc); }), "accumulate");
     }
@@ -834,7 +929,8 @@ pt_status pt_render_frame_noalloc(pt_ctx* c, const pt_render_args* a, float* img
     Launch L;
     st = launch_config(c, a, L);
     if (st) return st;
-    const WsLayout w = layout(c, a, L);
+    WsLayout w = layout(c, a, L);
+    if (w.total > kNoAllocScratchBytes) w = layout(c, a, L, Use::kStages);  // without a small frame's rows
     if (w.total > kNoAllocScratchBytes)
         return fail(PT_ENOMEM, "the frame needs " + std::to_string(w.total) + " bytes of device scratch, more than the " +
                                    std::to_string(kNoAllocScratchBytes) +
@@ -857,7 +953,7 @@ pt_status pt_frames_workspace_size(pt_ctx* c, const pt_render_args* a, uint64_t*
     Launch L;
     pt_status st = launch_config(c, a, L);
     if (st) return st;
-    *bytes = (uint64_t)c->in_flight * frame_slot_bytes(c, layout(c, a, L));
+    *bytes = (uint64_t)c->in_flight * frame_slot_bytes(c, layout(c, a, L, Use::kInFlight));
     return PT_OK;
 }
 
@@ -874,7 +970,7 @@ pt_status pt_render_frames(pt_ctx* c, const pt_render_args* a, int32_t n_frames,
     Launch L;
     st = launch_config(c, a, L);
     if (st) return st;
-    const WsLayout w = layout(c, a, L);
+    const WsLayout w = layout(c, a, L, Use::kInFlight);
     const size_t slot = frame_slot_bytes(c, w);
     const int nf = c->in_flight;
     if (ws_bytes < (uint64_t)nf * slot) return fail(PT_ENOMEM, "workspace too small (pt_frames_workspace_size)");
@@ -910,7 +1006,7 @@ pt_status pt_render_frames(pt_ctx* c, const pt_render_args* a, int32_t n_frames,
         PT_HIP(hipEventRecord(c->ev_stage[k], c->aux[k]), "record event");
         PT_HIP(hipStreamWaitEvent(s, c->ev_stage[k], 0), "stream wait");
         PathParams pp{af.spp, af.max_depth, af.nee ? 1 : 0, af.rr_start, af.seed, af.frame, af.job, af.sampler};
-        if (a->mode == PT_MODE_WAVE) PT_HIP(launch_accumulate(dim3(L.grid), dim3(L.block), s, c->cam, pp, Lbuf, img, acc), "accumulate");
+        if (Lbuf) PT_HIP(launch_accumulate(dim3(L.grid), dim3(L.block), s, c->cam, pp, Lbuf, img, acc), "accumulate");
         else PT_HIP(launch_average(dim3(L.grid), dim3(L.block), s, frame_img, npix, af.frame, img, acc), "average");
         PT_HIP(hipEventRecord(c->ev_acc[k], s), "record event");
     }
@@ -930,7 +1026,7 @@ pt_status pt_render_backward(pt_ctx* c, const pt_render_args* a, const float* d_
     Launch L;
     st = launch_config(c, a, L);
     if (st) return st;
-    WsLayout w = layout(c, a, L, true);
+    WsLayout w = layout(c, a, L, Use::kBackward);
     if (ws_bytes < w.total) return fail(PT_ENOMEM, "workspace too small (pt_backward_workspace_size)");
     PT_HIP(hipSetDevice(c->device), "hipSetDevice");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -956,7 +1052,7 @@ pt_status pt_render_backward(pt_ctx* c, const pt_render_args* a, const float* d_
         // counts its rays in the block after the cursors
         PT_HIP(launch_init_counts(s, reinterpret_cast<uint32_t*>(cursor), 8, 0u), "init path cursors");
         hipStream_t s2 = nullptr;
-        if (!(a->flags & PT_FLAG_SERIAL_STAGES)) {
+        if (!(a->flags & PT_FLAG_SERIAL_STAGES) && !w.small_grid) {
             st = side_stream(c, 2 * (a->max_depth + 1), s2);
             if (st) return st;
         }
@@ -1003,9 +1099,14 @@ pt_status pt_frame_stats_get(pt_ctx* c, pt_frame_stats* out) {
         out->launches[t.stage] += 1;
     }
     std::vector<uint32_t> h(c->last_ncounts);
-    PT_HIP(hipMemcpy(h.data(), c->last_counts, h.size() * sizeof(uint32_t), hipMemcpyDeviceToHost), "read counters");
-    unsigned long long tv[kTravWords / 2];
-    PT_HIP(hipMemcpy(tv, c->last_trav, sizeof tv, hipMemcpyDeviceToHost), "read work counters");
+    unsigned long long tv[kTravWords / 2] = {};
+    if (c->last_rows) {
+        const pt_status rs = small_counts(c, h);
+        if (rs) return rs;
+    } else {
+        PT_HIP(hipMemcpy(h.data(), c->last_counts, h.size() * sizeof(uint32_t), hipMemcpyDeviceToHost), "read counters");
+        PT_HIP(hipMemcpy(tv, c->last_trav, sizeof tv, hipMemcpyDeviceToHost), "read work counters");
+    }
     const uint64_t npix = c->last_npix, npaths = npix * (uint64_t)c->last_spp;
     const double img_bytes = 12.0 + (c->last_acc ? 24.0 : 0.0);  // image write (+ running average RMW)
     if (c->last_kind != 1) {

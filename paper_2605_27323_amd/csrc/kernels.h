@@ -116,6 +116,19 @@ hipError_t launch_accumulate(dim3 grid, dim3 block, hipStream_t s, const CamView
 hipError_t launch_average(dim3 grid, dim3 block, hipStream_t s, const float* I, uint32_t npix, uint32_t frame,
                           float* img, float* acc);
 
+// Small frames (small.h): whole paths in one launch, of at most kSmallDepth
+// scattering vertices.  Rows of ray counts hold small_row_words(D) words.
+constexpr int kSmallDepth = 62;
+constexpr int kSmallBlock = 128;  // a workgroup: a wave of paths and one of light samples
+__host__ __device__ inline uint32_t small_row_words(int D) { return 2u * ((uint32_t)D + 2u) + 1u; }
+struct SmallArgs {
+    uint32_t npaths, per;  // the frame's paths, and how many go to a wave at a time
+    float *img, *acc;      // image and running average (or null)
+    uint32_t *rows, *err;  // ray counts per workgroup; overflow flag (or null)
+};
+hipError_t launch_small(int lds, uint32_t grid, hipStream_t s, const SceneView& sc, const CamView& cam,
+                        const PathParams& pp, const SmallArgs& sa, const WaveBufs& wb, uint2* ovf, int gcap);
+
 struct BatchBufs;
 hipError_t launch_batch_init(hipStream_t s, const BatchBufs& bb, uint32_t total);
 hipError_t launch_batch_iteration(int lds, dim3 grid, dim3 block, hipStream_t s, const BatchBufs& bb, int q,

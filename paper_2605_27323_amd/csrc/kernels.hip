@@ -4,6 +4,7 @@
 // path state, live paths compacted into a queue after every bounce).
 #include "wavefront.h"
 #include "wave.h"
+#include "small.h"
 
 namespace ptmi {
 
@@ -14,26 +15,6 @@ __device__ __forceinline__ TravStack<LDS, COUNT> make_stack(uint32_t* smem, uint
                                                             uint32_t nlanes) {
     return make_trav_stack<LDS, COUNT>(reinterpret_cast<uint2*>(smem), (int)blockDim.x, ovf, gtid,
                                        (int)nlanes, gcap);
-}
-
-// Stage the light table (CDF words, leaf-order and input triangle indices)
-// in the block's LDS so that the light choice is a binary search in LDS.
-// Every thread of the block must call this (it synchronises the block).
-__device__ __forceinline__ LightCache stage_lights(const SceneView& sc, uint32_t* buf) {
-    if (sc.nl <= 0 || sc.nl > kLdsLights) return no_light_cache();
-    for (int j = threadIdx.x; j < sc.nl; j += blockDim.x) {
-        const LightEntry e = sc.lights[j];
-        buf[j] = e.cdf;
-        buf[kLdsLights + j] = e.tri;
-        buf[2 * kLdsLights + j] = e.id;
-    }
-    __syncthreads();
-    LightCache lc;
-    lc.cdf = (const lds_u32*)buf;
-    lc.tri = (const lds_u32*)(buf + kLdsLights);
-    lc.id = (const lds_u32*)(buf + 2 * kLdsLights);
-    lc.n = sc.nl;
-    return lc;
 }
 
 }  // namespace

@@ -6,6 +6,8 @@
 
 #include <cstdint>
 
+#include "device.h"
+
 namespace ptmi {
 
 __device__ __forceinline__ uint32_t lane_id() {
@@ -140,6 +142,26 @@ __device__ __forceinline__ void block_reserve2(BlockReserve& br, int par, uint32
     }
     j0 = o0 + rank_in(m0);
     j1 = o1 + rank_in(m1);
+}
+
+// Stage the light table (CDF words, leaf-order and input triangle indices)
+// in the block's LDS so that the light choice is a binary search in LDS.
+// Every thread of the block must call this (it synchronises the block).
+__device__ __forceinline__ LightCache stage_lights(const SceneView& sc, uint32_t* buf) {
+    if (sc.nl <= 0 || sc.nl > kLdsLights) return no_light_cache();
+    for (int j = threadIdx.x; j < sc.nl; j += blockDim.x) {
+        const LightEntry e = sc.lights[j];
+        buf[j] = e.cdf;
+        buf[kLdsLights + j] = e.tri;
+        buf[2 * kLdsLights + j] = e.id;
+    }
+    __syncthreads();
+    LightCache lc;
+    lc.cdf = (const lds_u32*)buf;
+    lc.tri = (const lds_u32*)(buf + kLdsLights);
+    lc.id = (const lds_u32*)(buf + 2 * kLdsLights);
+    lc.n = sc.nl;
+    return lc;
 }
 
 }  // namespace ptmi
