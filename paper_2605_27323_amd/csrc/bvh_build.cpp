@@ -27,6 +27,11 @@ struct BNode {
     float lo[3], hi[3];
     BNode* kid[2];
     int32_t first, count;  // count > 0: leaf
+    // of the collapse (plan_collapse): the subtree's cost in at most j + 1
+    // slots of a parent, and how many of them the first child gets (0: one
+    // slot fewer is better)
+    float cost[4];
+    uint8_t left[4];
 };
 
 struct Arena {
@@ -43,6 +48,41 @@ float area_of(const float lo[3], const float hi[3]) {
     float dx = hi[0] - lo[0], dy = hi[1] - lo[1], dz = hi[2] - lo[2];
     if (!(dx >= 0.f) || !(dy >= 0.f) || !(dz >= 0.f)) return 0.f;
     return 2.f * (dx * dy + dy * dz + dz * dx);
+}
+
+// The 4-wide tree of least expected node visits over a binary one, by the
+// dynamic program of Wald, Benthin and Boulos ("Getting rid of packets",
+// 2008, sec. 3.2): cost[j] is the least sum of node areas that represents n
+// in at most j + 1 slots of its parent.  Called when both children have it.
+void plan_collapse(BNode* n) {
+    if (n->count > 0 || n->kid[0] == nullptr) {
+        for (int j = 0; j < 4; ++j) {
+            n->cost[j] = 0.f;
+            n->left[j] = 0;
+        }
+        return;
+    }
+    const BNode *l = n->kid[0], *r = n->kid[1];
+    float split[4];  // the two children in j + 1 slots
+    uint8_t left[4];
+    for (int j = 1; j < 4; ++j) {
+        split[j] = INFINITY;
+        left[j] = 1;
+        for (int k = 1; k <= j; ++k) {
+            const float c = l->cost[k - 1] + r->cost[j - k];
+            if (c < split[j]) {
+                split[j] = c;
+                left[j] = (uint8_t)k;
+            }
+        }
+    }
+    n->cost[0] = area_of(n->lo, n->hi) + split[3];
+    n->left[0] = left[3];
+    for (int j = 1; j < 4; ++j) {
+        const bool open = split[j] <= n->cost[j - 1];  // the shallower one of two equals
+        n->cost[j] = open ? split[j] : n->cost[j - 1];
+        n->left[j] = open ? left[j] : 0;
+    }
 }
 
 class BinaryBuilder {
@@ -75,6 +115,7 @@ class BinaryBuilder {
         n->first = first;
         n->count = count;
         n->kid[0] = n->kid[1] = nullptr;
+        plan_collapse(n);
         return n;
     }
 
@@ -174,6 +215,7 @@ class BinaryBuilder {
             n->kid[0] = rec(first, nl, arena);
             n->kid[1] = rec(mid, nr, arena);
         }
+        plan_collapse(n);
         return n;
     }
 };
@@ -246,9 +288,21 @@ void quantize_node(Node4& q, const float lo[4][3], const float hi[4][3], const u
     for (int s = 0; s < 4; ++s) q.ref[s] = ref[s];
 }
 
+// Which children a 4-wide node gets: of least expected node visits
+// (plan_collapse) from kPlanTris triangles on, below that by opening the
+// child of largest area until four are there.  Traversal is bound by the
+// nodes visited, and the plan has 1 to 3 % less time at 100k to 2M triangles
+// (1920 x 1080, 2M triangles: 2.15 -> 2.13 ms, with attributes 1.31 -> 1.28,
+// 4000 instances 5.56 -> 5.46, a batch of eight 400k-triangle renders 2.50 ->
+// 2.44; host build of 2M triangles as before).  At 1k to 40k the two are even.
+// A room of 36 triangles is bound by the longest path through the tree
+// instead, which opening by area keeps shorter (256 x 256: 86 us, planned 94).
+constexpr int32_t kPlanTris = 512;
+
 struct Collapser {
     std::vector<Node4>& out;
     float pad;
+    bool planned;
     int depth = 0;
 
     static bool is_leaf(const BNode* n) { return n->count > 0 || (n->kid[0] == nullptr); }
@@ -265,12 +319,28 @@ struct Collapser {
         return kLeafBit | (uint32_t(n->count - 1) << kLeafCountShift) | uint32_t(n->first);
     }
 
+    // the children that represent n in at most `slots` slots of its parent
+    static void gather(const BNode* n, int slots, const BNode* kids[4], int& k) {
+        while (slots > 1 && n->left[slots - 1] == 0) --slots;
+        if (slots == 1 || is_leaf(n)) {
+            kids[k++] = n;
+            return;
+        }
+        gather(n->kid[0], n->left[slots - 1], kids, k);
+        gather(n->kid[1], slots - n->left[slots - 1], kids, k);
+    }
+
     // Writes node `idx` from the binary subtree rooted at internal node n.
     void emit(uint32_t idx, const BNode* n, int level) {
         depth = std::max(depth, level);
         const BNode* kids[4] = {n->kid[0], n->kid[1], nullptr, nullptr};
         int k = 2;
-        while (k < 4) {
+        if (planned) {
+            k = 0;
+            gather(n->kid[0], n->left[0], kids, k);
+            gather(n->kid[1], 4 - n->left[0], kids, k);
+        }
+        while (!planned && k < 4) {  // open the internal child of largest area
             int best = -1;
             float ba = -1.f;
             for (int i = 0; i < k; ++i) {
@@ -346,7 +416,7 @@ BuildResult build_scene(const std::vector<float>& tri_v, const std::vector<int32
     for (int32_t i = 0; i < nt; ++i) order[i] = i;
     r.nodes.reserve(nt / 2 + 1);
     r.nodes.emplace_back();
-    Collapser col{r.nodes, pad};
+    Collapser col{r.nodes, pad, nt >= kPlanTris};
     if (nt == 0) {
         const float lo[4][3] = {}, hi[4][3] = {};
         const uint32_t ref[4] = {kEmptyRef, kEmptyRef, kEmptyRef, kEmptyRef};
@@ -464,8 +534,8 @@ namespace {
 // A binary subtree collapsed into nodes[idx] (and nodes appended for its
 // internal children); a single leaf is wrapped in a node with one child.
 // Returns the depth in BVH4 levels.
-int emit_tree(std::vector<Node4>& nodes, uint32_t idx, BNode* root, float pad) {
-    Collapser col{nodes, pad};
+int emit_tree(std::vector<Node4>& nodes, uint32_t idx, BNode* root, float pad, bool planned) {
+    Collapser col{nodes, pad, planned};
     if (Collapser::is_leaf(root)) {
         float lo[4][3] = {}, hi[4][3] = {};
         const uint32_t ref[4] = {root->count > 0 ? Collapser::leaf_ref(root) : kEmptyRef, kEmptyRef, kEmptyRef,
@@ -492,6 +562,7 @@ BuildResult build_instanced(const std::vector<float>& tri_v, const std::vector<i
     BuildResult r;
     const int32_t nt = (int32_t)tri_mat.size();
     const int nmesh = (int)is.mesh_first.size(), ninst = (int)is.inst_mesh.size();
+    const bool planned = (int64_t)nt + ninst >= kPlanTris;  // the meshes' triangles and their instances
     max_leaf = std::max(1, std::min(kMaxLeaf, max_leaf));
     if (threads <= 0) threads = (int)std::max(1u, std::thread::hardware_concurrency());
 
@@ -526,7 +597,7 @@ BuildResult build_instanced(const std::vector<float>& tri_v, const std::vector<i
         BNode* root = bb.build(first, count);
         const uint32_t idx = (uint32_t)r.nodes.size();
         r.nodes.emplace_back();
-        blas_depth = std::max(blas_depth, emit_tree(r.nodes, idx, root, pad));
+        blas_depth = std::max(blas_depth, emit_tree(r.nodes, idx, root, pad, planned));
         mesh_root[m] = idx;
         for (int a = 0; a < 3; ++a) {
             mlo[3 * m + a] = (double)std::nextafter(root->lo[a] - pad, -INFINITY);
@@ -582,7 +653,7 @@ BuildResult build_instanced(const std::vector<float>& tri_v, const std::vector<i
     } else {
         BinaryBuilder tb(iinfo, iorder, 1, threads);
         BNode* root = tb.build();
-        tlas_depth = emit_tree(r.nodes, 0, root, 0.f);
+        tlas_depth = emit_tree(r.nodes, 0, root, 0.f, planned);
         for (int a = 0; a < 3; ++a) {
             r.center[a] = (float)(0.5 * (wlo[a] + whi[a]));
             r.max_coord = std::max(r.max_coord, (float)std::max(std::fabs(wlo[a]), std::fabs(whi[a])));
