@@ -10,6 +10,23 @@ namespace ptmi {
 
 namespace {
 
+// The sums that a wave collects before it adds them to global memory: per
+// pending triangle three channel values, its place in the gradient and one
+// byte of a table that finds equal places.
+constexpr int kMergeSlots = 128;
+struct MergeBuf {
+    float v[3 * 64];
+    uint32_t at[64];
+    uint8_t slot[kMergeSlots];
+};
+static_assert(sizeof(MergeBuf) <= 9 * 64 * sizeof(uint2), "the wave's stack rows hold it (8 and the discard row)");
+
+// order of the wave's own LDS accesses (they execute in order; this keeps the compiler from moving them)
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Gradients go to global memory with hardware fp32 atomics, except two
 // kinds of hot spots, which each block sums in LDS and adds once at the
 // end: the light-sample emission terms of lights in the first kLdsLights
@@ -17,24 +34,78 @@ namespace {
 // them), and the albedo and emission terms of the kHotTris largest
 // triangles (a ground plane or an area light is reached by a large share
 // of all paths, and atomics on a few addresses are served one at a time).
+// The others wait in registers for flush(), once per vertex.  Added one by
+// one they bound replay B from records: 5.60 ms for a whole backward of 2.1M
+// paths (512 x 512, 8 samples) over 1.02M triangles, 3.94 with them left out,
+// since every lane of every instruction is a request of its own.  With three
+// neighbouring lanes for the three channels of a triangle, which are one
+// request, 4.51; with the wave's equal triangles (samples of one pixel) merged
+// before, 4.04 (replay B 2.27 -> 0.80).  More than one copy of the sums in LDS
+// gained nothing.
 struct AtomicAcc {
     float* lds_light;  // 3 floats per light (local memory of the block)
     uint32_t n_lds;    // lights kept there
     float* lds_hot;    // [albedo, emission][3 * kHotTris] sums of the largest triangles
     uint32_t n_hot;
-    __device__ __forceinline__ void add_tri(uint32_t hot, int which, int c, float* p, float v) {
-        if (v == 0.0f) return;
-        if (hot - 1u < n_hot)
-            atomicAdd(&lds_hot[which * 3 * kHotTris + 3 * (hot - 1u) + (uint32_t)c], v);
-        else
-            unsafeAtomicAdd(p, v);
+    float* g[2];       // albedo and emission gradient
+    uint32_t at[2];    // this lane's pending triangle in g: 3 * id (kNone: none)
+    float v[2][3];     // and its values
+    static constexpr uint32_t kNone = 0xFFFFFFFFu;
+
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            at[w] = kNone;
+            v[w][0] = v[w][1] = v[w][2] = 0.0f;
+        }
     }
-    __device__ __forceinline__ void add_light(uint32_t j, int c, float* p, float v) {
-        if (v == 0.0f) return;
+    __device__ __forceinline__ void add_tri(uint32_t hot, int which, int c, float* p, float x) {
+        if (x == 0.0f) return;
+        if (hot - 1u < n_hot) {
+            atomicAdd(&lds_hot[which * 3 * kHotTris + 3 * (hot - 1u) + (uint32_t)c], x);
+        } else {
+            at[which] = (uint32_t)(p - g[which]) - (uint32_t)c;
+            v[which][c] = x;
+        }
+    }
+    __device__ __forceinline__ void add_light(uint32_t j, int c, float* p, float x) {
+        if (x == 0.0f) return;
         if (j < n_lds)
-            atomicAdd(&lds_light[3 * j + (uint32_t)c], v);
+            atomicAdd(&lds_light[3 * j + (uint32_t)c], x);
         else
-            unsafeAtomicAdd(p, v);
+            unsafeAtomicAdd(p, x);
+    }
+    // by all lanes of the wave together
+    __device__ __forceinline__ void flush(int which, MergeBuf& m) {
+        const bool has = at[which] != kNone;
+        const uint64_t all = __ballot(has);
+        if (all == 0ull) return;
+        const uint32_t lane = lane_id(), me = rank_in(all), n = (uint32_t)__popcll(all);
+        const uint32_t h = (at[which] * 2654435761u) >> 25;
+        if (has) {
+            m.at[me] = at[which];
+            m.slot[h] = (uint8_t)me;  // one of the lanes that share it stays
+#pragma unroll
+            for (int c = 0; c < 3; ++c) m.v[3 * me + c] = v[which][c];
+        }
+        wave_lds_order();
+        if (has) {
+            const uint32_t w = m.slot[h];
+            if (w != me && m.at[w] == at[which]) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    m.v[3 * me + c] = 0.0f;
+                    if (v[which][c] != 0.0f) atomicAdd(&m.v[3 * w + c], v[which][c]);
+                }
+            }
+        }
+        wave_lds_order();
+        for (uint32_t e = lane; e < 3u * n; e += 64u) {
+            const uint32_t t = e / 3u;
+            const float x = m.v[e];
+            if (x != 0.0f) unsafeAtomicAdd(g[which] + m.at[t] + (e - 3u * t), x);
+        }
+        wave_lds_order();
     }
 };
 
@@ -138,6 +209,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED
     acc.n_lds = (uint32_t)min(max(sc.nl, 0), kLdsLights);
     acc.lds_hot = hot_g;
     acc.n_hot = (uint32_t)min(max(sc.n_hot, 0), kHotTris);
+    acc.g[0] = g_alb;
+    acc.g[1] = g_emi;
+    // replay B traces no ray while it adds, so the wave's stack rows serve
+    // as its merge buffer
+    constexpr uint32_t kWaveLds = STORED ? (uint32_t)sizeof(MergeBuf) : (uint32_t)(LDS + 1) * kStackRow;
+    MergeBuf& merge = *reinterpret_cast<MergeBuf*>(reinterpret_cast<char*>(smem) + (threadIdx.x >> 6) * kWaveLds);
     for (uint32_t j = threadIdx.x; j < 3 * acc.n_lds; j += blockDim.x) light_g[j] = 0.0f;
     for (uint32_t j = threadIdx.x; j < 2 * 3 * kHotTris; j += blockDim.x) hot_g[j] = 0.0f;
     __syncthreads();
@@ -181,9 +258,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED
             if (drained) break;
             continue;
         }
-        if (!live) continue;
-        if (!adjoint_b_step<LDS, ATTR, AtomicAcc, false, STORED>(sc, pp, ar, g_alb, g_emi, st, acc, ne, ns, rec))
-            live = false;
+        acc.clear();
+        if (live)
+            live = adjoint_b_step<LDS, ATTR, AtomicAcc, false, STORED>(sc, pp, ar, g_alb, g_emi, st, acc, ne, ns, rec);
+        acc.flush(0, merge);
+        acc.flush(1, merge);
     }
     // with count_rays (replay A ran as the wavefront, which keeps its own
     // counters) the paths' rays are counted here (traced here, or by
@@ -241,8 +320,8 @@ hipError_t launch_adjoint(int lds, dim3 grid, dim3 block, hipStream_t s, const S
                           const PathParams& pp, const float* d_img, const float4* Lpath, unsigned long long* cursor,
                           float* g_alb, float* g_emi, uint2* ovf, int gcap, uint32_t* stats, int count_rays,
                           const VertexRecs& rec) {
-    // with the records replay B traces nothing: no traversal stack in LDS
-    const size_t sm = rec.hit ? 0 : trav_stack_lds_bytes(lds, (int)block.x);
+    // with the records replay B traces nothing: no traversal stack in LDS, merge buffers only
+    const size_t sm = rec.hit ? sizeof(MergeBuf) * (block.x / 64u) : trav_stack_lds_bytes(lds, (int)block.x);
 #define K(N, A, S)                                                                                               \
     hipLaunchKernelGGL((k_adjoint<N, A, S>), grid, block, sm, s, sc, cam, pp, d_img, Lpath, cursor, g_alb, g_emi, \
                        ovf, gcap, stats, count_rays, rec)
