@@ -113,12 +113,13 @@ struct AtomicAcc {
 
 // Replay A of every path: its radiance, into Lpath[path].  One loop trip =
 // one path vertex; a lane whose path is done takes the next path of its
-// wave's chunk, a wave whose chunk is used up takes the next 64 paths from
-// cursor[0].  Five waves per SIMD, as the megakernel.  STORE: every
+// workgroup's share (wave.h).  A cursor of all workgroups in global memory is
+// served one wave at a time, about 11 ns each: with 122880 paths it was most
+// of replay B (see there).  Five waves per SIMD, as the megakernel.  STORE: every
 // vertex's intersection and light-sample visibility go to rec as well.
 template <int LDS, bool ATTR, bool STORE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k_adjoint_radiance(
-    SceneView sc, CamView cam, PathParams pp, float4* __restrict__ Lpath, unsigned long long* __restrict__ cursor,
+    SceneView sc, CamView cam, PathParams pp, float4* __restrict__ Lpath, uint32_t simds,
     uint2* __restrict__ ovf, int gcap, uint32_t* __restrict__ stats, VertexRecs rec) {
     extern __shared__ __align__(8) uint32_t smem[];
     const uint32_t nlanes = gridDim.x * blockDim.x;
@@ -126,41 +127,31 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k
     TravStack<LDS> st =
         make_trav_stack<LDS>(reinterpret_cast<uint2*>(smem), (int)blockDim.x, ovf, gtid, (int)nlanes, gcap);
     const uint32_t npaths = (uint32_t)cam.W * (uint32_t)cam.H * (uint32_t)pp.spp;
-    uint32_t next = 0, end = 0;  // wave-uniform
-    bool drained = false;        // wave-uniform
+    __shared__ uint32_t cursor;
+    const BlockShare share = open_share(npaths, simds, &cursor);
+    bool more = share.first < share.hi;  // the share holds further paths (wave-uniform)
+    uint32_t want = share.start;         // paths to take next at most
     bool live = false;
     uint32_t path = 0, pix = 0, sample = 0, ne = 0, ns = 0;
     PathRun pr;
     while (true) {
         const uint64_t idle = __ballot(!live);
-        if (idle != 0ull && !drained) {
-            if (next >= end) {
-                unsigned long long base = 0ull;
-                if (lane_id() == 0) base = atomicAdd(cursor, 64ull);
-                base = wave_broadcast_u64(base);
-                if (base >= (unsigned long long)npaths) {
-                    drained = true;
-                } else {
-                    next = (uint32_t)base;
-                    end = (uint32_t)min(base + 64ull, (unsigned long long)npaths);
-                }
-            }
-            if (!drained) {
-                if (!live) {
-                    const uint32_t p = next + rank_in(idle);
-                    if (p < end) {
-                        path = p;
-                        pix = p / (uint32_t)pp.spp;
-                        sample = pp.frame * (uint32_t)pp.spp + (p - pix * (uint32_t)pp.spp);
-                        path_begin(cam, pp, pix, sample, pr);
-                        live = true;
-                    }
-                }
-                next = min(next + (uint32_t)__popcll(idle), end);
+        const uint32_t nidle = (uint32_t)__popcll(idle);
+        if (more && nidle > 0u) {
+            const uint32_t n = min(nidle, want), c = share.take<true>(n, more);
+            want = 64u;
+            const uint32_t r = rank_in(idle);
+            const uint64_t p = share.at_wide(c + r);
+            if (!live && r < n && p < share.hi) {
+                path = (uint32_t)p;
+                pix = path / (uint32_t)pp.spp;
+                sample = pp.frame * (uint32_t)pp.spp + (path - pix * (uint32_t)pp.spp);
+                path_begin(cam, pp, pix, sample, pr);
+                live = true;
             }
         }
         if (__ballot(live) == 0ull) {
-            if (drained) break;
+            if (!more) break;
             continue;
         }
         if (!live) continue;
@@ -186,15 +177,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k
 }
 
 // Replay B of every path, one vertex per loop trip with the same hand-out
-// of paths (cursor[1]), from the radiance replay A left in Lpath.  STORED:
-// from replay A's records too, tracing no ray (no traversal stack, so its
-// register budget is set on its own).
+// of paths, from the radiance replay A left in Lpath.  STORED: from replay
+// A's records too, tracing no ray (no traversal stack, so its register budget
+// is set on its own).  Bound by the instructions of shading a vertex: 2.1M
+// paths of the 1.02M-triangle scene 0.80 -> 0.72 ms, and 122880 paths of a room
+// (four bounces) 104 -> 77 us, when the paths came from the workgroups' shares
+// instead of one global cursor.  Three waves per SIMD: 0.79 ms and 71 us, five
+// 1.2; refilling only once 16 or 32 lanes are idle the same or slower.
 constexpr int kStoredWaves = 4;
 
 template <int LDS, bool ATTR, bool STORED>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED ? kStoredWaves : 4))) k_adjoint(SceneView sc, CamView cam, PathParams pp,
                                                  const float* __restrict__ d_img, const float4* __restrict__ Lpath,
-                                                 unsigned long long* __restrict__ cursor, float* __restrict__ g_alb,
+                                                 uint32_t simds, float* __restrict__ g_alb,
                                                  float* __restrict__ g_emi, uint2* __restrict__ ovf, int gcap,
                                                  uint32_t* __restrict__ stats, int count_rays, VertexRecs rec) {
     extern __shared__ __align__(8) uint32_t smem[];
@@ -220,42 +215,32 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED
     __syncthreads();
     const uint32_t npaths = (uint32_t)cam.W * (uint32_t)cam.H * (uint32_t)pp.spp;
     const float fs = (float)pp.spp;
-    uint32_t next = 0, end = 0;  // wave-uniform
-    bool drained = false;        // wave-uniform
+    __shared__ uint32_t cursor;
+    const BlockShare share = open_share(npaths, simds, &cursor);
+    bool more = share.first < share.hi;  // the share holds further paths (wave-uniform)
+    uint32_t want = share.start;         // paths to take next at most
     bool live = false;
     AdjRun ar;
     uint32_t ne = 0, ns = 0;
     while (true) {
         const uint64_t idle = __ballot(!live);
-        if (idle != 0ull && !drained) {
-            if (next >= end) {
-                unsigned long long base = 0ull;
-                if (lane_id() == 0) base = atomicAdd(cursor + 1, 64ull);
-                base = wave_broadcast_u64(base);
-                if (base >= (unsigned long long)npaths) {
-                    drained = true;
-                } else {
-                    next = (uint32_t)base;
-                    end = (uint32_t)min(base + 64ull, (unsigned long long)npaths);
-                }
-            }
-            if (!drained) {
-                if (!live) {
-                    const uint32_t p = next + rank_in(idle);
-                    if (p < end) {
-                        const uint32_t pix = p / (uint32_t)pp.spp;
-                        const uint32_t s = p - pix * (uint32_t)pp.spp;
-                        const f3 delta = mk3(d_img[3 * (size_t)pix] / fs, d_img[3 * (size_t)pix + 1] / fs,
-                                             d_img[3 * (size_t)pix + 2] / fs);
-                        adjoint_b_begin(cam, pp, pix, pp.frame * (uint32_t)pp.spp + s, delta, xyz(Lpath[p]), ar, p);
-                        live = true;
-                    }
-                }
-                next = min(next + (uint32_t)__popcll(idle), end);
+        const uint32_t nidle = (uint32_t)__popcll(idle);
+        if (more && nidle > 0u) {
+            const uint32_t n = min(nidle, want), c = share.take<true>(n, more);
+            want = 64u;
+            const uint32_t r = rank_in(idle);
+            const uint64_t at = share.at_wide(c + r);
+            if (!live && r < n && at < share.hi) {
+                const uint32_t p = (uint32_t)at, pix = p / (uint32_t)pp.spp;
+                const uint32_t s = p - pix * (uint32_t)pp.spp;
+                const f3 delta = mk3(d_img[3 * (size_t)pix] / fs, d_img[3 * (size_t)pix + 1] / fs,
+                                     d_img[3 * (size_t)pix + 2] / fs);
+                adjoint_b_begin(cam, pp, pix, pp.frame * (uint32_t)pp.spp + s, delta, xyz(Lpath[p]), ar, p);
+                live = true;
             }
         }
         if (__ballot(live) == 0ull) {
-            if (drained) break;
+            if (!more) break;
             continue;
         }
         acc.clear();
@@ -294,11 +279,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED
 
 hipError_t launch_adjoint_radiance(int lds, dim3 grid, dim3 block, hipStream_t s, const SceneView& sc,
                                    const CamView& cam, const PathParams& pp, float4* Lpath,
-                                   unsigned long long* cursor, uint2* ovf, int gcap, uint32_t* stats,
+                                   uint32_t simds, uint2* ovf, int gcap, uint32_t* stats,
                                    const VertexRecs& rec) {
     size_t sm = trav_stack_lds_bytes(lds, (int)block.x);
 #define K(N, A, S) \
-    hipLaunchKernelGGL((k_adjoint_radiance<N, A, S>), grid, block, sm, s, sc, cam, pp, Lpath, cursor, ovf, gcap, stats, rec)
+    hipLaunchKernelGGL((k_adjoint_radiance<N, A, S>), grid, block, sm, s, sc, cam, pp, Lpath, simds, ovf, gcap, stats, rec)
 #define X(N)                                                  \
     if (lds == N) {                                           \
         if (rec.hit) {                                        \
@@ -317,13 +302,13 @@ hipError_t launch_adjoint_radiance(int lds, dim3 grid, dim3 block, hipStream_t s
 }
 
 hipError_t launch_adjoint(int lds, dim3 grid, dim3 block, hipStream_t s, const SceneView& sc, const CamView& cam,
-                          const PathParams& pp, const float* d_img, const float4* Lpath, unsigned long long* cursor,
+                          const PathParams& pp, const float* d_img, const float4* Lpath, uint32_t simds,
                           float* g_alb, float* g_emi, uint2* ovf, int gcap, uint32_t* stats, int count_rays,
                           const VertexRecs& rec) {
     // with the records replay B traces nothing: no traversal stack in LDS, merge buffers only
     const size_t sm = rec.hit ? sizeof(MergeBuf) * (block.x / 64u) : trav_stack_lds_bytes(lds, (int)block.x);
 #define K(N, A, S)                                                                                               \
-    hipLaunchKernelGGL((k_adjoint<N, A, S>), grid, block, sm, s, sc, cam, pp, d_img, Lpath, cursor, g_alb, g_emi, \
+    hipLaunchKernelGGL((k_adjoint<N, A, S>), grid, block, sm, s, sc, cam, pp, d_img, Lpath, simds, g_alb, g_emi, \
                        ovf, gcap, stats, count_rays, rec)
     if (rec.hit) {
         if (sc.attr_flags) K(8, true, true);

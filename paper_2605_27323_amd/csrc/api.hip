@@ -158,6 +158,7 @@ struct WsLayout {
     size_t counts, trav, ovf, ovf2, adj, rec_hit, rec_vis, wave[11], sort_key, perm, hist, rows, total;
     int ncounts;
     uint32_t small_grid, small_per;  // a small frame's workgroups and paths per chunk (0: not a small frame)
+    bool keep;                       // backward: replay A leaves its records for replay B
 };
 constexpr int kTravWords = 16;  // 8 u64 traversal work counters
 
@@ -193,8 +194,8 @@ void plan_small(const pt_ctx* c, const pt_render_args* a, Use use, WsLayout& w) 
     w.small_grid = (uint32_t)((npaths + per - 1) / per);
 }
 
-// workspace: counters | traversal overflow stack | adjoint path cursors and
-// radiance (backward only) | wavefront state (wavefront only)
+// workspace: counters | traversal overflow stack | replay B's counters and the
+// path radiance (backward only) | wavefront state (wavefront only)
 WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use use = Use::kFrame) {
     WsLayout w{};
     const bool backward = use == Use::kBackward;
@@ -218,8 +219,7 @@ WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use u
     const bool wave_mode = a->mode == PT_MODE_WAVE;
     w.ovf2 = off;
     if (wave_mode) off = align_up(off + sizeof(uint2) * (size_t)L.gcap * L.nlanes);
-    // the adjoint's two path cursors and replay B's counters (one aligned
-    // block), then the per-path radiance when replay A runs as the
+    // replay B's counters (one aligned block), then the per-path radiance when replay A runs as the
     // megakernel-style kernel (as the wavefront it is the wavefront's
     // per-path radiance buffer)
     const bool wave = a->mode == PT_MODE_WAVE;
@@ -236,6 +236,7 @@ WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use u
         w.wave[i] = off;
         if (wave) off = align_up(off + sizeof(float4) * npaths);
     }
+    w.keep = keep;
     w.sort_key = off;
     if (wave) off = align_up(off + sizeof(uint32_t) * npaths);
     w.perm = off;
@@ -1022,11 +1023,11 @@ pt_status pt_render_backward(pt_ctx* c, const pt_render_args* a, const float* d_
     if (!d_image || !d_albedo || !d_emission) return fail(PT_EINVAL, "null gradient buffer");
     if (!ws) return fail(PT_EINVAL, "null workspace");
     if ((reinterpret_cast<uintptr_t>(ws) % kAlign) != 0) return fail(PT_EINVAL, "workspace must be 256-byte aligned");
-    const bool keep = (a->flags & PT_FLAG_KEEP_HITS) != 0;
     Launch L;
     st = launch_config(c, a, L);
     if (st) return st;
     WsLayout w = layout(c, a, L, Use::kBackward);
+    const bool keep = w.keep;
     if (ws_bytes < w.total) return fail(PT_ENOMEM, "workspace too small (pt_backward_workspace_size)");
     PT_HIP(hipSetDevice(c->device), "hipSetDevice");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -1040,17 +1041,25 @@ pt_status pt_render_backward(pt_ctx* c, const pt_render_args* a, const float* d_
     c->event_next = 0;
     PT_HIP(launch_init_counts(s, counts, w.ncounts, 0u), "init counters");
     PT_HIP(launch_init_counts(s, reinterpret_cast<uint32_t*>(trav), kTravWords, 0u), "init work counters");
-    unsigned long long* cursor = reinterpret_cast<unsigned long long*>(base + w.adj);
+    const uint32_t simds = (uint32_t)c->num_cu * kSimdsPerCu;
+    // no more workgroups than the shares of open_share fill (64 paths a wave,
+    // fewer where there are fewer than one wave per SIMD): a grid of 2048
+    // for the 480 of 122880 paths took 171 us, the 480 104
+    const size_t npaths = (size_t)c->cam.W * c->cam.H * a->spp;
+    const size_t per_wave = std::min<size_t>(64, std::max<size_t>(1, npaths / simds));
+    const size_t per_block = per_wave * ((size_t)L.block / 64);
+    const dim3 agrid((uint32_t)std::min<size_t>((size_t)L.grid, (npaths + per_block - 1) / per_block));
     const float4* Lpath = nullptr;
     const VertexRecs rec{keep ? reinterpret_cast<uint2*>(base + w.rec_hit) : nullptr,
                          keep ? reinterpret_cast<uint8_t*>(base + w.rec_vis) : nullptr,
-                         (uint32_t)((size_t)c->cam.W * c->cam.H * a->spp)};
+                         (uint32_t)npaths};
     if (a->mode == PT_MODE_WAVE) {
         // replay A by the wavefront stages (bit-identical per-path radiance;
         // the hybrid tail and the other wavefront options apply), which
         // leave each path's radiance in their per-path buffer; replay B
-        // counts its rays in the block after the cursors
-        PT_HIP(launch_init_counts(s, reinterpret_cast<uint32_t*>(cursor), 8, 0u), "init path cursors");
+        // counts its rays in a block of its own
+        counts = reinterpret_cast<uint32_t*>(base + w.adj);
+        PT_HIP(launch_init_counts(s, counts, 4, 0u), "init counters");
         hipStream_t s2 = nullptr;
         if (!(a->flags & PT_FLAG_SERIAL_STAGES) && !w.small_grid) {
             st = side_stream(c, 2 * (a->max_depth + 1), s2);
@@ -1058,19 +1067,17 @@ pt_status pt_render_backward(pt_ctx* c, const pt_render_args* a, const float* d_
         }
         st = enqueue_stages(c, a, L, w, base, s, nullptr, nullptr, prof, &Lpath, keep ? &rec : nullptr, s2);
         if (st) return st;
-        counts = reinterpret_cast<uint32_t*>(base + w.adj) + 4;
     } else {
         float4* Lp = reinterpret_cast<float4*>(base + w.adj + kAlign);
-        PT_HIP(launch_init_counts(s, reinterpret_cast<uint32_t*>(cursor), 4, 0u), "init path cursors");
         PT_HIP(timed(c, prof, 9, s, [&] {
-                   return launch_adjoint_radiance(L.lds, dim3(L.grid), dim3(L.block), s, c->view, c->cam, pp, Lp,
-                                                  cursor, ovf, L.gcap, counts, rec);
+                   return launch_adjoint_radiance(L.lds, agrid, dim3(L.block), s, c->view, c->cam, pp, Lp, simds, ovf,
+                                                  L.gcap, counts, rec);
                }),
                "adjoint replay A");
         Lpath = Lp;
     }
     PT_HIP(timed(c, prof, 7, s, [&] {
-               return launch_adjoint(L.lds, dim3(L.grid), dim3(L.block), s, c->view, c->cam, pp, d_image, Lpath, cursor,
+               return launch_adjoint(L.lds, agrid, dim3(L.block), s, c->view, c->cam, pp, d_image, Lpath, simds,
                                      d_albedo, d_emission, ovf, L.gcap, counts, a->mode == PT_MODE_WAVE ? 1 : 0, rec);
            }),
            "adjoint replay B");

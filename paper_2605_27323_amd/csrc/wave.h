@@ -73,13 +73,19 @@ struct BlockShare {
     __device__ __forceinline__ uint32_t at(uint32_t c) const {
         return first + (c >> lg) * stride + (c & ((1u << lg) - 1u));
     }
+    // the same where the queue may end within a section per workgroup of 2^32
+    __device__ __forceinline__ uint64_t at_wide(uint32_t c) const {
+        return (uint64_t)first + (uint64_t)(c >> lg) * stride + (c & ((1u << lg) - 1u));
+    }
     // the next n entries of the share, for this wave: the index of the first
     // (wave-uniform); more = false once the share holds no further ones
+    template <bool WIDE = false>
     __device__ __forceinline__ uint32_t take(uint32_t n, bool& more) const {
         uint32_t c = 0;
         if (lane_id() == 0) c = __hip_atomic_fetch_add(cursor, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         c = __builtin_amdgcn_readfirstlane(c);
-        more = at(c + n) < hi;
+        if constexpr (WIDE) more = at_wide(c + n) < hi;
+        else more = at(c + n) < hi;
         return c;
     }
 };
