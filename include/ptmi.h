@@ -242,7 +242,8 @@ typedef struct {
  * tail_spread: 1 = the hybrid tail spreads its queue over as many waves as
  * the device holds at once (partly filled waves, more latency hidden: faster
  * when a frame runs alone), 0 = full waves (fewer instructions: faster with
- * frames in flight); same image bit for bit.
+ * frames in flight), except a short queue of a frame by itself; same image
+ * bit for bit.
  * mega_waves: the megakernel's occupancy, 4 (0 = default) or 5 waves per
  * SIMD (more registers spilled: slower frame by frame, faster with frames in
  * flight); same image bit for bit. */

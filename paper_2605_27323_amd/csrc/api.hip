@@ -354,7 +354,7 @@ pt_status side_stream(pt_ctx* c, int nev, hipStream_t& out) {
 // waits for it.  The image is the same bit for bit.
 pt_status enqueue_stages(pt_ctx* c, const pt_render_args* a, const Launch& L, const WsLayout& w, char* base,
                          hipStream_t s, float* img, float* acc, bool prof, const float4** Lbuf,
-                         const VertexRecs* rec = nullptr, hipStream_t s2 = nullptr) {
+                         const VertexRecs* rec = nullptr, hipStream_t s2 = nullptr, bool in_flight = false) {
     uint32_t* counts = reinterpret_cast<uint32_t*>(base + w.counts);
     unsigned long long* trav = reinterpret_cast<unsigned long long*>(base + w.trav);
     uint2* ovf = reinterpret_cast<uint2*>(base + w.ovf);
@@ -429,6 +429,15 @@ pt_status enqueue_stages(pt_ctx* c, const pt_render_args* a, const Launch& L, co
         PT_HIP(timed(c, prof, 0, s, [&] { return launch_raygen(grid, block, s, c->cam, pp, wb); }), "raygen");
         uint2* ovf2 = reinterpret_cast<uint2*>(base + w.ovf2);
         const bool fork = s2 != nullptr && a->nee;
+        // A frame by itself spreads the hybrid tail's queue over all resident
+        // waves, asked to or not, when it fills at most half of their lanes:
+        // the tail is a few paths' serial chains, and a wave goes as slowly as
+        // the slowest of its lanes (tails of 86k and 111k paths, frames of
+        // 1.02M triangles 2152 -> 2086 us, of 4000 instances 5445 -> 5342; of 231k
+        // paths 5631 -> 5564, but a backward's 3960 -> 4012).  Frames in flight
+        // fill the device with their stages (12.05 -> 12.82 ms for eight).
+        const uint32_t tail_waves = (uint32_t)c->num_cu * kTailWavesPerCu;
+        const uint32_t spread_most = a->tail_spread ? 0xFFFFFFFFu : in_flight ? 0u : tail_waves * 32u;
         int pend = -1;  // bounce whose shadow stage runs on s2, not yet joined
         int64_t promotes = 0;
         if (wb.two_slot) {
@@ -453,7 +462,7 @@ pt_status enqueue_stages(pt_ctx* c, const pt_render_args* a, const Launch& L, co
             if (compact && tail)
                 PT_HIP(timed(c, prof, 8, s, [&] {
                            return launch_tail(L.lds, count, grid, block, s, c->view, pp, wb, b, sort, tail, ovf, L.gcap,
-                                              a->tail_spread ? (uint32_t)c->num_cu * kTailWavesPerCu : 0u);
+                                              tail_waves, spread_most);
                        }),
                        "hybrid tail");
             if (last) break;
@@ -1012,7 +1021,7 @@ pt_status pt_render_frames(pt_ctx* c, const pt_render_args* a, int32_t n_frames,
         // the slot's previous frame must have been accumulated
         PT_HIP(hipStreamWaitEvent(c->aux[k], c->ev_acc[k], 0), "stream wait");
         const float4* Lbuf = nullptr;
-        st = enqueue_stages(c, &af, L, w, base, c->aux[k], frame_img, nullptr, false, &Lbuf);
+        st = enqueue_stages(c, &af, L, w, base, c->aux[k], frame_img, nullptr, false, &Lbuf, nullptr, nullptr, true);
         if (st) return st;
         PT_HIP(hipEventRecord(c->ev_stage[k], c->aux[k]), "record event");
         PT_HIP(hipStreamWaitEvent(s, c->ev_stage[k], 0), "stream wait");

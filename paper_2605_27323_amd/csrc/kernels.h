@@ -85,12 +85,12 @@ hipError_t launch_extend(int lds, bool count, dim3 grid, dim3 block, hipStream_t
 // skipped here and finished in place by launch_tail
 hipError_t launch_shade(dim3 grid, dim3 block, hipStream_t s, const SceneView& sc, const PathParams& pp,
                         const WaveBufs& wb, int b, int compact, int sorted, uint32_t tail);
-// resident_waves: 0 = queue entries in full waves; else the waves the
-// device holds at once at the tail kernel's occupancy, over which a short
-// queue is spread
+// resident_waves: the waves the device holds at once at the tail kernel's
+// occupancy, over which a queue of at most spread_most paths is spread; a
+// longer one goes into full waves
 hipError_t launch_tail(int lds, bool count, dim3 grid, dim3 block, hipStream_t s, const SceneView& sc,
                        const PathParams& pp, const WaveBufs& wb, int b, int sorted, uint32_t tail, uint2* ovf,
-                       int gcap, uint32_t resident_waves);
+                       int gcap, uint32_t resident_waves, uint32_t spread_most);
 // counting sort of queue b by a 6-bit key when it holds >= threshold
 // paths: key_kind 0 = material of the hit (for shade), 1 = ray direction
 // octant and origin side (for extend)

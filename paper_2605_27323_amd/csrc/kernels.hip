@@ -159,9 +159,10 @@ __global__ void k_promote(WaveBufs wb, int b) {
 template <int LDS, bool COUNT, bool INST, bool ATTR>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_shade_tail(SceneView sc, PathParams pp, WaveBufs wb, int b, int sorted,
                                                     uint32_t tail, uint2* __restrict__ ovf, int gcap,
-                                                    uint32_t spread) {
+                                                    uint32_t spread, uint32_t spread_most) {
     const uint32_t count = wb.counts[live_slot(wb, b)];
     if (!(count < tail) || count == 0u) return;
+    if (count > spread_most) spread = 0u;
     extern __shared__ __align__(8) uint32_t smem[];
     __shared__ uint32_t light_buf[3 * kLdsLights];
     const LightCache lc = stage_lights(sc, light_buf);
@@ -566,10 +567,10 @@ hipError_t launch_shade(dim3 grid, dim3 block, hipStream_t s, const SceneView& s
 
 hipError_t launch_tail(int lds, bool count, dim3 grid, dim3 block, hipStream_t s, const SceneView& sc,
                        const PathParams& pp, const WaveBufs& wb, int b, int sorted, uint32_t tail, uint2* ovf,
-                       int gcap, uint32_t resident_waves) {
+                       int gcap, uint32_t resident_waves, uint32_t spread_most) {
     const size_t sm = stack_lds_bytes(lds, block.x);
-    const uint32_t spread = resident_waves ? std::max(1u, std::min(grid.x * block.x / 64u, resident_waves)) : 0u;
-#define L(N, C, I, A) hipLaunchKernelGGL((k_shade_tail<N, C, I, A>), grid, block, sm, s, sc, pp, wb, b, sorted, tail, ovf, gcap, spread);
+    const uint32_t spread = std::max(1u, std::min(grid.x * block.x / 64u, resident_waves));
+#define L(N, C, I, A) hipLaunchKernelGGL((k_shade_tail<N, C, I, A>), grid, block, sm, s, sc, pp, wb, b, sorted, tail, ovf, gcap, spread, spread_most);
 #define X(N) PT_DISPATCH_SHADE(N, L)
     PT_STACK_CASES(X)
 #undef X
