@@ -368,7 +368,7 @@ pt_status pt_render_frames(pt_ctx* ctx, const pt_render_args* args, int32_t n_fr
  * keeps every vertex's intersection and light-sample visibility and the
  * second traces no ray (same gradients, 9 bytes per path vertex of
  * workspace).
- * workspace: at least pt_backward_workspace_size bytes (ray counters, the
+ * workspace: at least pt_backward_workspace_size bytes (path cursors, the
  * per-path radiance, the wavefront buffers in PT_MODE_WAVE, the kept
  * records with PT_FLAG_KEEP_HITS, the traversal stack overflow area),
  * 256-byte aligned.

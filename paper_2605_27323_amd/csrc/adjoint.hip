@@ -2,6 +2,8 @@
 // radiance, kept per path), then replay B from the same random numbers,
 // gradients added with hardware fp32 atomics (see adjoint.h for the
 // algorithm).
+#include <type_traits>
+
 #include "adjoint.h"
 #include "wave.h"
 #include "kernels.h"
@@ -109,17 +111,87 @@ struct AtomicAcc {
     }
 };
 
+// How a replay's waves come by their paths, the next ones for the idle lanes of
+// a wave (ballot idle, nidle of them); all lanes of the wave call take, which
+// returns whether this lane gets path p, and more is false once there are none.
+//
+// The tracing replays: from a cursor in global memory, 64 paths at a time,
+// since a path's rays take unequally long: 2.1M paths of the 1.02M-triangle
+// scene 8.57 ms a backward, from the workgroups' fixed shares 10.80.  Up to
+// two paths per lane of the grid, each wave's first 64 are dealt: all waves
+// would ask the cursor at once, and it serves one at a time (480000 paths of a
+// room 926 -> 786 us; of 50000 triangles 753 -> 635).  With more paths that
+// costs up to 5 % (8.57 -> 9.05 ms: waves that start together go on together).
+struct CursorPaths {
+    unsigned long long* cursor;  // zero when the kernel starts
+    uint32_t dealt;              // paths dealt before
+    uint32_t npaths, next, end;  // the wave's 64
+    bool more;
+    __device__ __forceinline__ void open(unsigned long long* c, uint32_t n) {
+        const uint32_t lanes = gridDim.x * blockDim.x;
+        cursor = c;
+        npaths = n;
+        dealt = 0u;
+        next = end = 0u;
+        more = true;
+        if (n / 2u <= lanes) {
+            const uint32_t w = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+            const unsigned long long at = 64ull * __builtin_amdgcn_readfirstlane(w);
+            dealt = lanes;
+            end = (uint32_t)min(at + 64ull, (unsigned long long)n);
+            next = (uint32_t)min(at, (unsigned long long)end);
+        }
+    }
+    __device__ __forceinline__ bool take(uint64_t idle, uint32_t nidle, uint32_t& p) {
+        if (next >= end) {
+            unsigned long long base = 0ull;
+            if (lane_id() == 0 && dealt < npaths) base = atomicAdd(cursor, 64ull);
+            base = wave_broadcast_u64(base) + dealt;
+            if (base >= (unsigned long long)npaths) {
+                more = false;
+                return false;
+            }
+            next = (uint32_t)base;
+            end = (uint32_t)min(base + 64ull, (unsigned long long)npaths);
+        }
+        const uint32_t r = rank_in(idle), left = end - next;
+        p = next + r;
+        next += min(nidle, left);
+        return r < left;
+    }
+};
+
+// The replay from records, whose vertices all cost the same: from the
+// workgroup's share (wave.h).  The cursor is served one wave at a time, about
+// 11 ns each, which was most of this replay (see k_adjoint).
+struct SharePaths {
+    BlockShare share;
+    uint32_t want;  // paths to take next at most
+    bool more;
+    __device__ __forceinline__ void open(uint32_t n, uint32_t simds, uint32_t* cursor) {
+        share = open_share(n, simds, cursor);
+        more = share.first < share.hi;
+        want = share.start;
+    }
+    __device__ __forceinline__ bool take(uint64_t idle, uint32_t nidle, uint32_t& p) {
+        const uint32_t n = min(nidle, want), c = share.take<true>(n, more);
+        want = 64u;
+        const uint32_t r = rank_in(idle);
+        const uint64_t at = share.at_wide(c + r);
+        p = (uint32_t)at;
+        return r < n && at < share.hi;
+    }
+};
+
 }  // namespace
 
 // Replay A of every path: its radiance, into Lpath[path].  One loop trip =
 // one path vertex; a lane whose path is done takes the next path of its
-// workgroup's share (wave.h).  A cursor of all workgroups in global memory is
-// served one wave at a time, about 11 ns each: with 122880 paths it was most
-// of replay B (see there).  Five waves per SIMD, as the megakernel.  STORE: every
+// wave's 64 (cursor[0]).  Five waves per SIMD, as the megakernel.  STORE: every
 // vertex's intersection and light-sample visibility go to rec as well.
 template <int LDS, bool ATTR, bool STORE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k_adjoint_radiance(
-    SceneView sc, CamView cam, PathParams pp, float4* __restrict__ Lpath, uint32_t simds,
+    SceneView sc, CamView cam, PathParams pp, float4* __restrict__ Lpath, unsigned long long* __restrict__ cursor,
     uint2* __restrict__ ovf, int gcap, uint32_t* __restrict__ stats, VertexRecs rec) {
     extern __shared__ __align__(8) uint32_t smem[];
     const uint32_t nlanes = gridDim.x * blockDim.x;
@@ -127,23 +199,18 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k
     TravStack<LDS> st =
         make_trav_stack<LDS>(reinterpret_cast<uint2*>(smem), (int)blockDim.x, ovf, gtid, (int)nlanes, gcap);
     const uint32_t npaths = (uint32_t)cam.W * (uint32_t)cam.H * (uint32_t)pp.spp;
-    __shared__ uint32_t cursor;
-    const BlockShare share = open_share(npaths, simds, &cursor);
-    bool more = share.first < share.hi;  // the share holds further paths (wave-uniform)
-    uint32_t want = share.start;         // paths to take next at most
+    CursorPaths paths;
+    paths.open(cursor, npaths);
     bool live = false;
     uint32_t path = 0, pix = 0, sample = 0, ne = 0, ns = 0;
     PathRun pr;
     while (true) {
         const uint64_t idle = __ballot(!live);
         const uint32_t nidle = (uint32_t)__popcll(idle);
-        if (more && nidle > 0u) {
-            const uint32_t n = min(nidle, want), c = share.take<true>(n, more);
-            want = 64u;
-            const uint32_t r = rank_in(idle);
-            const uint64_t p = share.at_wide(c + r);
-            if (!live && r < n && p < share.hi) {
-                path = (uint32_t)p;
+        if (paths.more && nidle > 0u) {
+            uint32_t p = 0;
+            if (paths.take(idle, nidle, p) && !live) {
+                path = p;
                 pix = path / (uint32_t)pp.spp;
                 sample = pp.frame * (uint32_t)pp.spp + (path - pix * (uint32_t)pp.spp);
                 path_begin(cam, pp, pix, sample, pr);
@@ -151,7 +218,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k
             }
         }
         if (__ballot(live) == 0ull) {
-            if (!more) break;
+            if (!paths.more) break;
             continue;
         }
         if (!live) continue;
@@ -176,8 +243,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k
     if (st.overflow) atomicOr(&stats[2], 1u);
 }
 
-// Replay B of every path, one vertex per loop trip with the same hand-out
-// of paths, from the radiance replay A left in Lpath.  STORED: from replay
+// Replay B of every path, one vertex per loop trip (tracing, paths from
+// cursor[1]), from the radiance replay A left in Lpath.  STORED: from replay
 // A's records too, tracing no ray (no traversal stack, so its register budget
 // is set on its own).  Bound by the instructions of shading a vertex: 2.1M
 // paths of the 1.02M-triangle scene 0.80 -> 0.72 ms, and 122880 paths of a room
@@ -189,7 +256,8 @@ constexpr int kStoredWaves = 4;
 template <int LDS, bool ATTR, bool STORED>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED ? kStoredWaves : 4))) k_adjoint(SceneView sc, CamView cam, PathParams pp,
                                                  const float* __restrict__ d_img, const float4* __restrict__ Lpath,
-                                                 uint32_t simds, float* __restrict__ g_alb,
+                                                 unsigned long long* __restrict__ cursor, uint32_t simds,
+                                                 float* __restrict__ g_alb,
                                                  float* __restrict__ g_emi, uint2* __restrict__ ovf, int gcap,
                                                  uint32_t* __restrict__ stats, int count_rays, VertexRecs rec) {
     extern __shared__ __align__(8) uint32_t smem[];
@@ -215,23 +283,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED
     __syncthreads();
     const uint32_t npaths = (uint32_t)cam.W * (uint32_t)cam.H * (uint32_t)pp.spp;
     const float fs = (float)pp.spp;
-    __shared__ uint32_t cursor;
-    const BlockShare share = open_share(npaths, simds, &cursor);
-    bool more = share.first < share.hi;  // the share holds further paths (wave-uniform)
-    uint32_t want = share.start;         // paths to take next at most
+    __shared__ uint32_t share_cursor;
+    std::conditional_t<STORED, SharePaths, CursorPaths> paths;
+    if constexpr (STORED) paths.open(npaths, simds, &share_cursor);
+    else paths.open(cursor + 1, npaths);
     bool live = false;
     AdjRun ar;
     uint32_t ne = 0, ns = 0;
     while (true) {
         const uint64_t idle = __ballot(!live);
         const uint32_t nidle = (uint32_t)__popcll(idle);
-        if (more && nidle > 0u) {
-            const uint32_t n = min(nidle, want), c = share.take<true>(n, more);
-            want = 64u;
-            const uint32_t r = rank_in(idle);
-            const uint64_t at = share.at_wide(c + r);
-            if (!live && r < n && at < share.hi) {
-                const uint32_t p = (uint32_t)at, pix = p / (uint32_t)pp.spp;
+        if (paths.more && nidle > 0u) {
+            uint32_t p = 0;
+            if (paths.take(idle, nidle, p) && !live) {
+                const uint32_t pix = p / (uint32_t)pp.spp;
                 const uint32_t s = p - pix * (uint32_t)pp.spp;
                 const f3 delta = mk3(d_img[3 * (size_t)pix] / fs, d_img[3 * (size_t)pix + 1] / fs,
                                      d_img[3 * (size_t)pix + 2] / fs);
@@ -240,7 +305,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED
             }
         }
         if (__ballot(live) == 0ull) {
-            if (!more) break;
+            if (!paths.more) break;
             continue;
         }
         acc.clear();
@@ -279,11 +344,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED
 
 hipError_t launch_adjoint_radiance(int lds, dim3 grid, dim3 block, hipStream_t s, const SceneView& sc,
                                    const CamView& cam, const PathParams& pp, float4* Lpath,
-                                   uint32_t simds, uint2* ovf, int gcap, uint32_t* stats,
+                                   unsigned long long* cursor, uint2* ovf, int gcap, uint32_t* stats,
                                    const VertexRecs& rec) {
     size_t sm = trav_stack_lds_bytes(lds, (int)block.x);
 #define K(N, A, S) \
-    hipLaunchKernelGGL((k_adjoint_radiance<N, A, S>), grid, block, sm, s, sc, cam, pp, Lpath, simds, ovf, gcap, stats, rec)
+    hipLaunchKernelGGL((k_adjoint_radiance<N, A, S>), grid, block, sm, s, sc, cam, pp, Lpath, cursor, ovf, gcap, stats, rec)
 #define X(N)                                                  \
     if (lds == N) {                                           \
         if (rec.hit) {                                        \
@@ -302,13 +367,14 @@ hipError_t launch_adjoint_radiance(int lds, dim3 grid, dim3 block, hipStream_t s
 }
 
 hipError_t launch_adjoint(int lds, dim3 grid, dim3 block, hipStream_t s, const SceneView& sc, const CamView& cam,
-                          const PathParams& pp, const float* d_img, const float4* Lpath, uint32_t simds,
+                          const PathParams& pp, const float* d_img, const float4* Lpath, unsigned long long* cursor,
+                          uint32_t simds,
                           float* g_alb, float* g_emi, uint2* ovf, int gcap, uint32_t* stats, int count_rays,
                           const VertexRecs& rec) {
     // with the records replay B traces nothing: no traversal stack in LDS, merge buffers only
     const size_t sm = rec.hit ? sizeof(MergeBuf) * (block.x / 64u) : trav_stack_lds_bytes(lds, (int)block.x);
 #define K(N, A, S)                                                                                               \
-    hipLaunchKernelGGL((k_adjoint<N, A, S>), grid, block, sm, s, sc, cam, pp, d_img, Lpath, simds, g_alb, g_emi, \
+    hipLaunchKernelGGL((k_adjoint<N, A, S>), grid, block, sm, s, sc, cam, pp, d_img, Lpath, cursor, simds, g_alb, g_emi, \
                        ovf, gcap, stats, count_rays, rec)
     if (rec.hit) {
         if (sc.attr_flags) K(8, true, true);

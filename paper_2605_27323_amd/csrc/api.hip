@@ -194,8 +194,8 @@ void plan_small(const pt_ctx* c, const pt_render_args* a, Use use, WsLayout& w) 
     w.small_grid = (uint32_t)((npaths + per - 1) / per);
 }
 
-// workspace: counters | traversal overflow stack | replay B's counters and the
-// path radiance (backward only) | wavefront state (wavefront only)
+// workspace: counters | traversal overflow stack | adjoint path cursors and
+// radiance (backward only) | wavefront state (wavefront only)
 WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use use = Use::kFrame) {
     WsLayout w{};
     const bool backward = use == Use::kBackward;
@@ -219,7 +219,8 @@ WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use u
     const bool wave_mode = a->mode == PT_MODE_WAVE;
     w.ovf2 = off;
     if (wave_mode) off = align_up(off + sizeof(uint2) * (size_t)L.gcap * L.nlanes);
-    // replay B's counters (one aligned block), then the per-path radiance when replay A runs as the
+    // the adjoint's two path cursors and replay B's counters (one aligned
+    // block), then the per-path radiance when replay A runs as the
     // megakernel-style kernel (as the wavefront it is the wavefront's
     // per-path radiance buffer)
     const bool wave = a->mode == PT_MODE_WAVE;
@@ -1068,6 +1069,9 @@ pt_status pt_render_backward(pt_ctx* c, const pt_render_args* a, const float* d_
     const size_t per_wave = std::min<size_t>(64, std::max<size_t>(1, npaths / simds));
     const size_t per_block = per_wave * ((size_t)L.block / 64);
     const dim3 agrid((uint32_t)std::min<size_t>((size_t)L.grid, (npaths + per_block - 1) / per_block));
+    // the tracing replays' two path cursors, replay B's counters
+    unsigned long long* cursor = reinterpret_cast<unsigned long long*>(base + w.adj);
+    PT_HIP(launch_init_counts(s, reinterpret_cast<uint32_t*>(cursor), 8, 0u), "init path cursors");
     const float4* Lpath = nullptr;
     const VertexRecs rec{keep ? reinterpret_cast<uint2*>(base + w.rec_hit) : nullptr,
                          keep ? reinterpret_cast<uint8_t*>(base + w.rec_vis) : nullptr,
@@ -1076,9 +1080,8 @@ pt_status pt_render_backward(pt_ctx* c, const pt_render_args* a, const float* d_
         // replay A by the wavefront stages (bit-identical per-path radiance;
         // the hybrid tail and the other wavefront options apply), which
         // leave each path's radiance in their per-path buffer; replay B
-        // counts its rays in a block of its own
-        counts = reinterpret_cast<uint32_t*>(base + w.adj);
-        PT_HIP(launch_init_counts(s, counts, 4, 0u), "init counters");
+        // counts its rays in the block of the cursors
+        counts = reinterpret_cast<uint32_t*>(cursor + 2);
         hipStream_t s2 = nullptr;
         if (!(a->flags & PT_FLAG_SERIAL_STAGES) && !w.small_grid) {
             st = side_stream(c, 2 * (a->max_depth + 1), s2);
@@ -1089,14 +1092,14 @@ pt_status pt_render_backward(pt_ctx* c, const pt_render_args* a, const float* d_
     } else {
         float4* Lp = reinterpret_cast<float4*>(base + w.adj + kAlign);
         PT_HIP(timed(c, prof, 9, s, [&] {
-                   return launch_adjoint_radiance(L.lds, agrid, dim3(L.block), s, c->view, c->cam, pp, Lp, simds, ovf,
+                   return launch_adjoint_radiance(L.lds, agrid, dim3(L.block), s, c->view, c->cam, pp, Lp, cursor, ovf,
                                                   L.gcap, counts, rec);
                }),
                "adjoint replay A");
         Lpath = Lp;
     }
     PT_HIP(timed(c, prof, 7, s, [&] {
-               return launch_adjoint(L.lds, agrid, dim3(L.block), s, c->view, c->cam, pp, d_image, Lpath, simds,
+               return launch_adjoint(L.lds, agrid, dim3(L.block), s, c->view, c->cam, pp, d_image, Lpath, cursor, simds,
                                      d_albedo, d_emission, ovf, L.gcap, counts, a->mode == PT_MODE_WAVE ? 1 : 0, rec);
            }),
            "adjoint replay B");
