@@ -32,6 +32,7 @@ struct BNode {
     // slot fewer is better)
     float cost[4];
     uint8_t left[4];
+    uint16_t levels[2];  // 4-wide levels of the subtree: opened by area, planned (0: a leaf)
 };
 
 struct Arena {
@@ -50,16 +51,60 @@ float area_of(const float lo[3], const float hi[3]) {
     return 2.f * (dx * dy + dy * dz + dz * dx);
 }
 
+bool is_leaf(const BNode* n) { return n->count > 0 || n->kid[0] == nullptr; }
+
+// The children of a 4-wide node at the internal node n by opening the child
+// of largest area until four are there; returns how many there are.
+int kids_by_area(const BNode* n, const BNode* kids[4]) {
+    kids[0] = n->kid[0];
+    kids[1] = n->kid[1];
+    int k = 2;
+    while (k < 4) {
+        int best = -1;
+        float ba = -1.f;
+        for (int i = 0; i < k; ++i) {
+            if (is_leaf(kids[i])) continue;
+            float a = area_of(kids[i]->lo, kids[i]->hi);
+            if (a > ba) { ba = a; best = i; }
+        }
+        if (best < 0) break;
+        const BNode* b = kids[best];
+        kids[best] = b->kid[0];
+        kids[k++] = b->kid[1];
+    }
+    return k;
+}
+
+// the children that represent n in at most `slots` slots of its parent
+void gather(const BNode* n, int slots, const BNode* kids[4], int& k) {
+    while (slots > 1 && n->left[slots - 1] == 0) --slots;
+    if (slots == 1 || is_leaf(n)) {
+        kids[k++] = n;
+        return;
+    }
+    gather(n->kid[0], n->left[slots - 1], kids, k);
+    gather(n->kid[1], slots - n->left[slots - 1], kids, k);
+}
+
+// The children of a 4-wide node at the internal node n by the plan below.
+int kids_by_plan(const BNode* n, const BNode* kids[4]) {
+    int k = 0;
+    gather(n->kid[0], n->left[0], kids, k);
+    gather(n->kid[1], 4 - n->left[0], kids, k);
+    return k;
+}
+
 // The 4-wide tree of least expected node visits over a binary one, by the
 // dynamic program of Wald, Benthin and Boulos ("Getting rid of packets",
 // 2008, sec. 3.2): cost[j] is the least sum of node areas that represents n
 // in at most j + 1 slots of its parent.  Called when both children have it.
 void plan_collapse(BNode* n) {
-    if (n->count > 0 || n->kid[0] == nullptr) {
+    if (is_leaf(n)) {
         for (int j = 0; j < 4; ++j) {
             n->cost[j] = 0.f;
             n->left[j] = 0;
         }
+        n->levels[0] = n->levels[1] = 0;
         return;
     }
     const BNode *l = n->kid[0], *r = n->kid[1];
@@ -82,6 +127,13 @@ void plan_collapse(BNode* n) {
         const bool open = split[j] <= n->cost[j - 1];  // the shallower one of two equals
         n->cost[j] = open ? split[j] : n->cost[j - 1];
         n->left[j] = open ? left[j] : 0;
+    }
+    for (int way = 0; way < 2; ++way) {
+        const BNode* kids[4];
+        const int k = way ? kids_by_plan(n, kids) : kids_by_area(n, kids);
+        int deepest = 0;
+        for (int i = 0; i < k; ++i) deepest = std::max<int>(deepest, kids[i]->levels[way]);
+        n->levels[way] = (uint16_t)std::min(deepest + 1, 0xFFFF);
     }
 }
 
@@ -297,6 +349,10 @@ void quantize_node(Node4& q, const float lo[4][3], const float hi[4][3], const u
 // 2.44; host build of 2M triangles as before).  At 1k to 40k the two are even.
 // A room of 36 triangles is bound by the longest path through the tree
 // instead, which opening by area keeps shorter (256 x 256: 86 us, planned 94).
+// A planned tree is no deeper than the one opened by area: where it would be
+// (one or two levels, up to four in a triangle soup), nodes are opened by area
+// on the way.  The stacks of all lanes, and with them the workspaces and
+// what fits the scratch of pt_render_frame_noalloc, are sized by the depth.
 constexpr int32_t kPlanTris = 512;
 
 struct Collapser {
@@ -304,8 +360,6 @@ struct Collapser {
     float pad;
     bool planned;
     int depth = 0;
-
-    static bool is_leaf(const BNode* n) { return n->count > 0 || (n->kid[0] == nullptr); }
 
     // padded box of a child
     void child_box(const BNode* c, float lo[3], float hi[3]) const {
@@ -319,40 +373,15 @@ struct Collapser {
         return kLeafBit | (uint32_t(n->count - 1) << kLeafCountShift) | uint32_t(n->first);
     }
 
-    // the children that represent n in at most `slots` slots of its parent
-    static void gather(const BNode* n, int slots, const BNode* kids[4], int& k) {
-        while (slots > 1 && n->left[slots - 1] == 0) --slots;
-        if (slots == 1 || is_leaf(n)) {
-            kids[k++] = n;
-            return;
-        }
-        gather(n->kid[0], n->left[slots - 1], kids, k);
-        gather(n->kid[1], slots - n->left[slots - 1], kids, k);
-    }
-
-    // Writes node `idx` from the binary subtree rooted at internal node n.
-    void emit(uint32_t idx, const BNode* n, int level) {
+    // Writes node `idx` from the binary subtree rooted at internal node n, in
+    // at most `most` levels (no fewer than the shallower way to open n takes).
+    void emit(uint32_t idx, const BNode* n, int level, int most) {
         depth = std::max(depth, level);
-        const BNode* kids[4] = {n->kid[0], n->kid[1], nullptr, nullptr};
-        int k = 2;
-        if (planned) {
-            k = 0;
-            gather(n->kid[0], n->left[0], kids, k);
-            gather(n->kid[1], 4 - n->left[0], kids, k);
-        }
-        while (!planned && k < 4) {  // open the internal child of largest area
-            int best = -1;
-            float ba = -1.f;
-            for (int i = 0; i < k; ++i) {
-                if (is_leaf(kids[i])) continue;
-                float a = area_of(kids[i]->lo, kids[i]->hi);
-                if (a > ba) { ba = a; best = i; }
-            }
-            if (best < 0) break;
-            const BNode* b = kids[best];
-            kids[best] = b->kid[0];
-            kids[k++] = b->kid[1];
-        }
+        const BNode* kids[4];
+        int k = planned ? kids_by_plan(n, kids) : 0;
+        for (int i = 0; i < k; ++i)
+            if (std::min(kids[i]->levels[0], kids[i]->levels[1]) >= most) k = 0;
+        if (k == 0) k = kids_by_area(n, kids);
         // allocate the internal children first: emplace_back may move `out`
         uint32_t child_idx[4] = {0, 0, 0, 0};
         for (int s = 0; s < k; ++s) {
@@ -369,7 +398,7 @@ struct Collapser {
         }
         quantize_node(out[idx], lo, hi, ref);
         for (int s = 0; s < k; ++s)
-            if (!is_leaf(kids[s])) emit(child_idx[s], kids[s], level + 1);
+            if (!is_leaf(kids[s])) emit(child_idx[s], kids[s], level + 1, most - 1);
     }
 };
 
@@ -425,7 +454,7 @@ BuildResult build_scene(const std::vector<float>& tri_v, const std::vector<int32
     } else {
         BinaryBuilder bb(info, order, max_leaf, threads);
         BNode* root = bb.build();
-        if (Collapser::is_leaf(root)) {
+        if (is_leaf(root)) {
             // a single leaf: wrap it in a root node with one child
             float lo[4][3] = {}, hi[4][3] = {};
             const uint32_t ref[4] = {Collapser::leaf_ref(root), kEmptyRef, kEmptyRef, kEmptyRef};
@@ -433,7 +462,7 @@ BuildResult build_scene(const std::vector<float>& tri_v, const std::vector<int32
             quantize_node(r.nodes[0], lo, hi, ref);
             col.depth = 1;
         } else {
-            col.emit(0, root, 1);
+            col.emit(0, root, 1, root->levels[0]);
         }
         r.depth = col.depth;
     }
@@ -536,7 +565,7 @@ namespace {
 // Returns the depth in BVH4 levels.
 int emit_tree(std::vector<Node4>& nodes, uint32_t idx, BNode* root, float pad, bool planned) {
     Collapser col{nodes, pad, planned};
-    if (Collapser::is_leaf(root)) {
+    if (is_leaf(root)) {
         float lo[4][3] = {}, hi[4][3] = {};
         const uint32_t ref[4] = {root->count > 0 ? Collapser::leaf_ref(root) : kEmptyRef, kEmptyRef, kEmptyRef,
                                  kEmptyRef};
@@ -544,7 +573,7 @@ int emit_tree(std::vector<Node4>& nodes, uint32_t idx, BNode* root, float pad, b
         quantize_node(nodes[idx], lo, hi, ref);
         return 1;
     }
-    col.emit(idx, root, 1);
+    col.emit(idx, root, 1, root->levels[0]);
     return col.depth;
 }
 
