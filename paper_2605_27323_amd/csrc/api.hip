@@ -158,13 +158,14 @@ struct WsLayout {
     size_t counts, trav, ovf, ovf2, adj, rec_hit, rec_vis, wave[11], sort_key, perm, hist, rows, total;
     int ncounts;
     uint32_t small_grid, small_per;  // a small frame's workgroups and paths per chunk (0: not a small frame)
+    bool small_next;                 // it has more chunks than workgroups
     bool keep;                       // backward: replay A leaves its records for replay B
 };
 constexpr int kTravWords = 16;  // 8 u64 traversal work counters
 
 // what a workspace is laid out for: a frame by itself, one of the frames in
-// flight, a backward; kStages: a frame that may not run as k_small
-enum class Use { kFrame, kInFlight, kBackward, kStages };
+// flight, a backward
+enum class Use { kFrame, kInFlight, kBackward };
 
 // Whether the frame (or the backward's first replay) runs as k_small, and
 // how: one path per lane, `small_per` of them to a wave, whole pixels of an
@@ -180,23 +181,48 @@ enum class Use { kFrame, kInFlight, kBackward, kStages };
 // : 2437, 692 : 558, 831 : 929.  Frames in flight, whose stages overlap, eight
 // frames: 64000 paths 2471 : 1965, 811 : 569; 120000 paths 2881 : 2995, 954 :
 // 842; 256000 paths 4839 : 6493, 1511 : 1752.
-void plan_small(const pt_ctx* c, const pt_render_args* a, Use use, WsLayout& w) {
-    if (use == Use::kStages || (a->flags & ~(PT_FLAG_XCD_LOCAL | PT_FLAG_KEEP_HITS | PT_FLAG_SERIAL_STAGES))) return;
+//
+// Its stacks spill to memory that the stages would have used (spill_bytes),
+// so that a small frame asks for no larger workspace than a large one of the
+// same launch shape, but for its rows of ray counts.  A launch shape whose area
+// does not hold all chunks at once gets as many workgroups as the device runs
+// at a time, or as fit, and a cursor over the chunks (megakernel, grid_mult 4,
+// 349872 paths 1361 : 1145 us, 682 : 506; 519841 paths 1652 : 1571, 751 : 683).
+// With fewer workgroups than the device runs, only where they hold as many
+// paths as the launch shape has lanes for: the megakernel one per pixel, the
+// stages one per path (block 64, grid_mult 2, megakernel: 16384 pixels of 2
+// samples 1152 : 676 us, but 195000 of one 2195 : 2576 us).
+void plan_small(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use use, size_t spill_bytes, WsLayout& w) {
+    if (a->flags & ~(PT_FLAG_XCD_LOCAL | PT_FLAG_KEEP_HITS | PT_FLAG_SERIAL_STAGES)) return;
     const uint64_t npaths = (uint64_t)c->cam.W * c->cam.H * (uint64_t)a->spp;
     const bool mega = a->mode == PT_MODE_MEGA, backward = use == Use::kBackward;
     const uint64_t most = use == Use::kInFlight ? 1u << 16 : (mega ? 1u << 19 : 3u << 16);
     if (npaths > most || a->max_depth > kSmallDepth) return;
     if (backward ? mega : a->spp > 64) return;
     const uint32_t simds = (uint32_t)c->num_cu * kSimdsPerCu, unit = backward ? 1u : (uint32_t)a->spp;
-    uint32_t per = std::min(64u, (uint32_t)((npaths + simds - 1) / simds));
+    const size_t group = sizeof(uint2) * (size_t)L.gcap * kSmallBlock;  // one workgroup's spill area
+    const uint32_t fit = group ? (uint32_t)std::min<size_t>(spill_bytes / group, 0x7FFFFFFFu) : 0x7FFFFFFFu;
+    const uint32_t waves = std::max(1u, std::min(simds, fit));
+    uint32_t per = std::min(64u, (uint32_t)((npaths + waves - 1) / waves));
     per = std::max(unit, per / unit * unit);
+    const uint32_t chunks = (uint32_t)((npaths + per - 1) / per);
+    uint32_t groups = chunks;
+    if (fit < chunks) {
+        const size_t lds = trav_stack_lds_bytes(L.lds, kSmallBlock) + kSmallLdsBytes;
+        const uint32_t resident = (uint32_t)c->num_cu * (uint32_t)std::min<size_t>(kSmallPerCu, c->lds_per_block / lds);
+        groups = std::min(fit, resident);
+        const uint64_t lanes = std::min<uint64_t>(L.nlanes, mega ? npaths / (uint64_t)a->spp : npaths);
+        if (groups < resident && (uint64_t)groups * per < lanes) return;
+    }
     w.small_per = per;
-    w.small_grid = (uint32_t)((npaths + per - 1) / per);
+    w.small_grid = groups;
+    w.small_next = groups < chunks;
 }
 
 // workspace: counters | traversal overflow stack | adjoint path cursors and
-// radiance (backward only) | wavefront state (wavefront only)
-WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use use = Use::kFrame) {
+// radiance (backward only) | wavefront state (wavefront only) | ray counts of
+// a small frame.  small = false: of the stages, however small the frame.
+WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use use = Use::kFrame, bool small = true) {
     WsLayout w{};
     const bool backward = use == Use::kBackward;
     const size_t npaths = (size_t)c->cam.W * c->cam.H * a->spp;
@@ -205,15 +231,13 @@ WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use u
     // two-slot count buffer (PT_FLAG_TWO_SLOT), the last word the overflow flag
     // (the megakernel's eight band cursors, u64, take words 8 .. 23)
     w.ncounts = std::max(2 * a->max_depth + 9, 24);
-    plan_small(c, a, use, w);
-    const size_t spill_lanes = std::max<size_t>(L.nlanes, (size_t)w.small_grid * kSmallBlock);
     size_t off = 0;
     w.counts = off;
     off = align_up(off + sizeof(uint32_t) * w.ncounts);
     w.trav = off;
     off = align_up(off + sizeof(uint32_t) * kTravWords);
     w.ovf = off;
-    off = align_up(off + sizeof(uint2) * (size_t)L.gcap * spill_lanes);
+    off = align_up(off + sizeof(uint2) * (size_t)L.gcap * L.nlanes);
     // the wavefront's shadow stage runs beside the next extend stage (on the
     // context's side stream) and spills its stacks to an area of its own
     const bool wave_mode = a->mode == PT_MODE_WAVE;
@@ -237,18 +261,6 @@ WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use u
         w.wave[i] = off;
         if (wave) off = align_up(off + sizeof(float4) * npaths);
     }
-    // A small replay A uses none of the stages' queues, so its records go
-    // there, flag or not, as long as they fit (9 bytes a vertex in 160 a path:
-    // up to depth 16), and replay B traces no ray: for 122880 paths of a room at
-    // depth 4 it took 218 us tracing and 171 from the records, now 77 (see
-    // k_adjoint); replay A 130 us either way.
-    w.keep = keep;
-    if (backward && wave && w.small_grid && !keep &&
-        align_up(sizeof(uint2) * nrec) + nrec <= w.wave[10] - w.wave[0]) {
-        w.rec_hit = w.wave[0];
-        w.rec_vis = w.rec_hit + align_up(sizeof(uint2) * nrec);
-        w.keep = true;
-    }
     w.sort_key = off;
     if (wave) off = align_up(off + sizeof(uint32_t) * npaths);
     w.perm = off;
@@ -256,9 +268,31 @@ WsLayout layout(const pt_ctx* c, const pt_render_args* a, const Launch& L, Use u
     w.hist = off;
     if (wave) off = align_up(off + sizeof(uint32_t) * (2 * kSortBins + 1));
     w.rows = off;
+    // A small frame uses none of this but the counters; a small replay A, the
+    // adjoint's block and the path radiance (the last queue) too.
+    if (small) plan_small(c, a, L, use, (backward ? w.adj : w.rows) - w.ovf, w);
+    // Nor does it use the stages' queues, so its records go there, flag or
+    // not, as long as they fit (9 bytes a vertex in 160 a path: up to depth
+    // 16), and replay B traces no ray: for 122880 paths of a room at depth 4 it
+    // took 218 us tracing and 171 from the records, now 77 (see k_adjoint);
+    // replay A 130 us either way.
+    w.keep = keep;
+    if (backward && wave && w.small_grid && !keep &&
+        align_up(sizeof(uint2) * nrec) + nrec <= w.wave[10] - w.wave[0]) {
+        w.rec_hit = w.wave[0];
+        w.rec_vis = w.rec_hit + align_up(sizeof(uint2) * nrec);
+        w.keep = true;
+    }
     if (w.small_grid) off = align_up(off + sizeof(uint32_t) * (size_t)small_row_words(a->max_depth) * w.small_grid);
     w.total = off;
     return w;
+}
+
+// The layout that a workspace of `bytes` holds: a small frame runs by the
+// stages where its rows of ray counts do not fit.
+WsLayout layout_within(const pt_ctx* c, const pt_render_args* a, const Launch& L, uint64_t bytes, Use use = Use::kFrame) {
+    const WsLayout w = layout(c, a, L, use);
+    return w.total <= bytes ? w : layout(c, a, L, use, false);
 }
 
 pt_status check_args(const pt_ctx* c, const pt_render_args* a) {
@@ -378,7 +412,9 @@ pt_status enqueue_stages(pt_ctx* c, const pt_render_args* a, const Launch& L, co
             wb.rec_vis = rec->vis;
             wb.rec_n = rec->npaths;
         }
-        const SmallArgs sa{npaths, w.small_per, img, acc, rows, img ? nullptr : counts + (w.ncounts - 1)};
+        const SmallArgs sa{npaths, w.small_per, img, acc, rows, img ? nullptr : counts + (w.ncounts - 1),
+                           w.small_next ? counts : nullptr};
+        if (sa.next) PT_HIP(launch_init_counts(s, counts, 1, 0u), "init chunk cursor");
         PT_HIP(launch_small(L.lds, w.small_grid, s, c->view, c->cam, pp, sa, wb, ovf, L.gcap), "small frame");
         remember_frame(c, a, counts, w.ncounts, a->mode == PT_MODE_MEGA ? 0 : 1, acc != nullptr);
         c->last_rows = rows;
@@ -920,7 +956,7 @@ pt_status pt_render_frame(pt_ctx* c, const pt_render_args* a, float* img, float*
     Launch L;
     st = launch_config(c, a, L);
     if (st) return st;
-    WsLayout w = layout(c, a, L);
+    const WsLayout w = layout_within(c, a, L, ws_bytes);
     if (ws_bytes < w.total) return fail(PT_ENOMEM, "workspace too small (pt_workspace_size)");
     PT_HIP(hipSetDevice(c->device), "hipSetDevice");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -951,8 +987,7 @@ pt_status pt_render_frame_noalloc(pt_ctx* c, const pt_render_args* a, float* img
     Launch L;
     st = launch_config(c, a, L);
     if (st) return st;
-    WsLayout w = layout(c, a, L);
-    if (w.total > kNoAllocScratchBytes) w = layout(c, a, L, Use::kStages);  // without a small frame's rows
+    const WsLayout w = layout_within(c, a, L, kNoAllocScratchBytes);
     if (w.total > kNoAllocScratchBytes)
         return fail(PT_ENOMEM, "the frame needs " + std::to_string(w.total) + " bytes of device scratch, more than the " +
                                    std::to_string(kNoAllocScratchBytes) +
@@ -992,9 +1027,10 @@ pt_status pt_render_frames(pt_ctx* c, const pt_render_args* a, int32_t n_frames,
     Launch L;
     st = launch_config(c, a, L);
     if (st) return st;
-    const WsLayout w = layout(c, a, L, Use::kInFlight);
-    const size_t slot = frame_slot_bytes(c, w);
     const int nf = c->in_flight;
+    WsLayout w = layout(c, a, L, Use::kInFlight);
+    if (ws_bytes < (uint64_t)nf * frame_slot_bytes(c, w)) w = layout(c, a, L, Use::kInFlight, false);
+    const size_t slot = frame_slot_bytes(c, w);
     if (ws_bytes < (uint64_t)nf * slot) return fail(PT_ENOMEM, "workspace too small (pt_frames_workspace_size)");
     PT_HIP(hipSetDevice(c->device), "hipSetDevice");
     if (!c->aux_ready) {
@@ -1047,7 +1083,7 @@ pt_status pt_render_backward(pt_ctx* c, const pt_render_args* a, const float* d_
     Launch L;
     st = launch_config(c, a, L);
     if (st) return st;
-    WsLayout w = layout(c, a, L, Use::kBackward);
+    const WsLayout w = layout_within(c, a, L, ws_bytes, Use::kBackward);
     const bool keep = w.keep;
     if (ws_bytes < w.total) return fail(PT_ENOMEM, "workspace too small (pt_backward_workspace_size)");
     PT_HIP(hipSetDevice(c->device), "hipSetDevice");

@@ -122,11 +122,14 @@ hipError_t launch_average(dim3 grid, dim3 block, hipStream_t s, const float* I, 
 // scattering vertices.  Rows of ray counts hold small_row_words(D) words.
 constexpr int kSmallDepth = 62;
 constexpr int kSmallBlock = 128;  // a workgroup: a wave of paths and one of light samples
+constexpr int kSmallLdsBytes = 15 * 1024;  // its LDS besides the traversal stacks
+constexpr int kSmallPerCu = 6;    // workgroups at a time on a compute unit (three waves per SIMD)
 __host__ __device__ inline uint32_t small_row_words(int D) { return 2u * ((uint32_t)D + 2u) + 1u; }
 struct SmallArgs {
     uint32_t npaths, per;  // the frame's paths, and how many go to a wave at a time
     float *img, *acc;      // image and running average (or null)
     uint32_t *rows, *err;  // ray counts per workgroup; overflow flag (or null)
+    uint32_t* next;        // chunks handed out beyond the first of every workgroup, zero before (or null: none)
 };
 hipError_t launch_small(int lds, uint32_t grid, hipStream_t s, const SceneView& sc, const CamView& cam,
                         const PathParams& pp, const SmallArgs& sa, const WaveBufs& wb, uint2* ovf, int gcap);

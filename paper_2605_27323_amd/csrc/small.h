@@ -42,8 +42,12 @@ __device__ __forceinline__ void pair_sync() {
 // slower; two the same).
 //
 // A chunk of sa.per paths (whole pixels when there is an image) goes to a
-// wave at a time.  sa.img: the pixels' means over their spp samples, added in
-// sample order (and the running average sa.acc); else wb.L: every path's
+// wave at a time, the first one by the workgroup's number.  Where there are
+// more chunks than workgroups (whose spill areas bound them), the next ones
+// come from a cursor, sa.next.
+//
+// sa.img: the pixels' means over their spp samples, added in sample order (and
+// the running average sa.acc); else wb.L: every path's
 // radiance.  wb.rec_*: the adjoint's kept intersections (or null).  The rays
 // traced per bounce go to sa.rows (extension rays of bounces 0 .. D + 1, light
 // samples of 0 .. D + 1, overflow flag), one row per workgroup: counters
@@ -55,6 +59,7 @@ __global__ void __launch_bounds__(kSmallBlock) __attribute__((amdgpu_waves_per_e
     extern __shared__ __align__(8) uint32_t smem[];
     __shared__ uint32_t light_buf[3 * kLdsLights];
     __shared__ PairShared ps2;
+    static_assert(sizeof light_buf + sizeof ps2 <= kSmallLdsBytes, "resident workgroups are counted by it");
     for (uint32_t j = threadIdx.x; j < 2u * (kSmallDepth + 2u); j += blockDim.x) (&ps2.rays[0][0])[j] = 0u;
     if (threadIdx.x == 0) ps2.overflow = 0u;
     __syncthreads();
@@ -81,8 +86,8 @@ __global__ void __launch_bounds__(kSmallBlock) __attribute__((amdgpu_waves_per_e
         return;
     }
     const uint32_t spp = (uint32_t)pp.spp;
-    for (uint32_t first = blockIdx.x * sa.per; first < sa.npaths; first += gridDim.x * sa.per) {
-        const uint32_t path = first + lane;
+    for (uint32_t chunk = blockIdx.x; (uint64_t)chunk * sa.per < sa.npaths;) {
+        const uint32_t path = chunk * sa.per + lane;
         const bool mine = lane < sa.per && path < sa.npaths;
         const uint32_t pix = path / spp, s = path - pix * spp;
         const uint32_t sample = pp.frame * spp + s;
@@ -145,6 +150,10 @@ __global__ void __launch_bounds__(kSmallBlock) __attribute__((amdgpu_waves_per_e
         } else if (mine) {
             wb.L[path] = make_float4(L.x, L.y, L.z, 0.f);
         }
+        if (sa.next == nullptr) break;
+        uint32_t taken = 0u;
+        if (lane == 0u) taken = atomicAdd(sa.next, 1u);
+        chunk = gridDim.x + __builtin_amdgcn_readfirstlane(taken);
     }
     if (lane == 0u) ps2.go = 0u;
     pair_sync();
