@@ -246,7 +246,19 @@ typedef struct {
  * bit for bit.
  * mega_waves: the megakernel's occupancy, 4 (0 = default) or 5 waves per
  * SIMD (more registers spilled: slower frame by frame, faster with frames in
- * flight); same image bit for bit. */
+ * flight); same image bit for bit.
+ *
+ * Small frames.  A frame of few paths (width x height x spp at most 2^19 in
+ * PT_MODE_MEGA, 3 * 2^16 in PT_MODE_WAVE, 2^16 for frames in flight; at most
+ * 64 samples a pixel and max_depth 62) runs as one launch of a kernel for
+ * such frames, and so does the first pass of a PT_MODE_WAVE adjoint of at
+ * most 3 * 2^16 paths, whatever its spp.  mode, block, grid_mult, tail_*,
+ * mega_waves, PT_FLAG_XCD_LOCAL and PT_FLAG_SERIAL_STAGES then choose no
+ * kernel (block and grid_mult bound its workspace, and with a launch shape too
+ * small for it the frame runs as in larger ones).  The image is the same bit
+ * for bit.  The flags PT_FLAG_PROFILE, PT_FLAG_COUNT_WORK,
+ * PT_FLAG_NO_COMPACT, PT_FLAG_SORT_MATERIAL, PT_FLAG_SORT_RAYS and
+ * PT_FLAG_TWO_SLOT keep the kernels that the arguments name. */
 typedef struct {
     int32_t spp, max_depth;
     uint64_t seed;
@@ -299,7 +311,10 @@ pt_status pt_set_camera(pt_ctx* ctx, const pt_camera* camera);
 /* Device workspace (bytes) a render with these arguments needs, for the
  * camera currently set: wavefront path state, queues and counters, and
  * the traversal stack overflow area (two of them in PT_MODE_WAVE: the
- * shadow stage has its own). */
+ * shadow stage has its own).  A small frame (pt_render_args) asks for the same
+ * and a row of ray counts per workgroup beside it, 8 max_depth + 20 bytes
+ * each; in a workspace without room for the rows it runs as a larger frame
+ * does (so the size with PT_FLAG_PROFILE is enough for the frame without). */
 pt_status pt_workspace_size(pt_ctx* ctx, const pt_render_args* args, uint64_t* bytes);
 
 /* Render one frame (paper Sec. 2.2 megakernel / Sec. 2.3 wavefront).
@@ -360,7 +375,9 @@ pt_status pt_render_frames(pt_ctx* ctx, const pt_render_args* args, int32_t n_fr
  * by (seed, frame, spp, job).  Each path is replayed twice from its random
  * numbers: a first pass over all paths keeps only each path's radiance (16
  * bytes per path in the workspace), a second pass replays them again and
- * adds the gradients; by default no vertex is stored.  args->mode selects how the
+ * adds the gradients; by default no vertex is stored, except by a small first
+ * pass (pt_render_args) up to max_depth 16, which has room for the records of
+ * PT_FLAG_KEEP_HITS in buffers that it does not use.  args->mode selects how the
  * first pass runs: PT_MODE_MEGA as one megakernel-style kernel, PT_MODE_WAVE
  * as the wavefront stages with the frame's wavefront options (hybrid tail,
  * sorts), whose per-path radiance is the same bit for bit; the second pass
@@ -388,7 +405,9 @@ pt_status pt_render_backward(pt_ctx* ctx, const pt_render_args* args, const floa
  *     filled only when the frame ran with PT_FLAG_PROFILE (else 0).
  *   stage_items[k]: work items the stage's launches processed (paths for
  *     raygen, accumulate pixels, queued rays for extend / shade / shadow /
- *     tail, paths for the megakernel and the adjoint); always filled.
+ *     tail, paths for the megakernel and the adjoint); always filled.  A
+ *     small frame (pt_render_args) launches none of these stages: its items
+ *     and bytes are those that the schedule of its arguments would have had.
  *   stage_bytes[k]: the stage's algorithmic path-state bytes (reads +
  *     writes of queue records, radiance and image buffers a stage must move;
  *     scene data excluded; conditional radiance updates of shade and shadow
@@ -450,7 +469,8 @@ pt_status pt_batch_workspace_size(const pt_job* jobs, int32_t n_jobs, const pt_b
 
 /* Render all jobs; returns when every image is written (synchronous).
  * job_ms (may be NULL): per job, device time from the start of the batch
- * to the moment its last path finished, in milliseconds. */
+ * to the end of the kernel in which its last path finished (jobs are
+ * counted off once per kernel and workgroup), in milliseconds. */
 pt_status pt_render_batch(const pt_job* jobs, int32_t n_jobs, const pt_batch_opts* opts, void* workspace,
                           uint64_t workspace_bytes, void* stream, double* job_ms, pt_batch_result* result);
 

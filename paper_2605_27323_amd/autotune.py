@@ -5,7 +5,9 @@ faster half is kept and re-timed with twice the repetitions, until one is
 left.  Results are cached in a JSON file keyed by the device, the workload
 shape and the schedule, so a later run with the same key reuses them.  Any
 parameter point renders the same image bit for bit (the parity tests check
-it), so tuning changes speed only.
+it), so tuning changes speed only.  A small frame (see pt_render_args in
+include/ptmi.h) runs as one launch at most points, which are then equally
+fast.
 """
 from __future__ import annotations
 
