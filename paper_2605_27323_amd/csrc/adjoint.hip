@@ -21,7 +21,7 @@ struct MergeBuf {
     uint32_t at[64];
     uint8_t slot[kMergeSlots];
 };
-static_assert(sizeof(MergeBuf) <= 9 * 64 * sizeof(uint2), "the wave's stack rows hold it (8 and the discard row)");
+static_assert(sizeof(MergeBuf) <= 8 * 64 * sizeof(uint2), "the wave's stack rows hold it (at least 8)");
 
 // order of the wave's own LDS accesses (they execute in order; this keeps the compiler from moving them)
 __device__ __forceinline__ void wave_lds_order() {
@@ -245,16 +245,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k
 
 // Replay B of every path, one vertex per loop trip (tracing, paths from
 // cursor[1]), from the radiance replay A left in Lpath.  STORED: from replay
-// A's records too, tracing no ray (no traversal stack, so its register budget
-// is set on its own).  Bound by the instructions of shading a vertex: 2.1M
-// paths of the 1.02M-triangle scene 0.80 -> 0.72 ms, and 122880 paths of a room
-// (four bounces) 104 -> 77 us, when the paths came from the workgroups' shares
-// instead of one global cursor.  Three waves per SIMD: 0.79 ms and 71 us, five
-// 1.2; refilling only once 16 or 32 lanes are idle the same or slower.
-constexpr int kStoredWaves = 4;
-
+// A's records too, tracing no ray; then bound by the instructions of shading a
+// vertex: 2.1M paths of the 1.02M-triangle scene 0.80 -> 0.72 ms, and 122880
+// paths of a room (four bounces) 104 -> 77 us, when the paths came from the
+// workgroups' shares instead of one global cursor.  Three waves per SIMD: 0.79
+// ms and 71 us, five 1.2; refilling only once 16 or 32 lanes are idle the same
+// or slower.
 template <int LDS, bool ATTR, bool STORED>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORED ? kStoredWaves : 4))) k_adjoint(SceneView sc, CamView cam, PathParams pp,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_adjoint(SceneView sc, CamView cam, PathParams pp,
                                                  const float* __restrict__ d_img, const float4* __restrict__ Lpath,
                                                  unsigned long long* __restrict__ cursor, uint32_t simds,
                                                  float* __restrict__ g_alb,

@@ -180,7 +180,12 @@ enum class Use { kFrame, kInFlight, kBackward };
 // against it: 512000 paths 1468 : 1472, 619 : 374, 768 : 574; 1036800 paths 2144
 // : 2437, 692 : 558, 831 : 929.  Frames in flight, whose stages overlap, eight
 // frames: 64000 paths 2471 : 1965, 811 : 569; 120000 paths 2881 : 2995, 954 :
-// 842; 256000 paths 4839 : 6493, 1511 : 1752.
+// 842; 256000 paths 4839 : 6493, 1511 : 1752.  Two-level scenes (4000 instances):
+// 189660 paths, stages 4044 : 1764, tuned tail 2583 : 1702; 519841 paths,
+// megakernel 3740 : 3673; eight frames of 64770 paths in flight 7161 : 5684.
+// Whole pixels of 33 to 63 samples fill a wave to half only: 33 samples of
+// 5700 pixels 1413 : 968, 652 : 215, 718 : 448, two-level 4042 : 2224; in the
+// megakernel, which takes a pixel's samples one after the other, 14756 : 966.
 //
 // Its stacks spill to memory that the stages would have used (spill_bytes),
 // so that a small frame asks for no larger workspace than a large one of the

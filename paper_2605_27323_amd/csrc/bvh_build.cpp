@@ -346,9 +346,12 @@ void quantize_node(Node4& q, const float lo[4][3], const float hi[4][3], const u
 // nodes visited, and the plan has 1 to 3 % less time at 100k to 2M triangles
 // (1920 x 1080, 2M triangles: 2.15 -> 2.13 ms, with attributes 1.31 -> 1.28,
 // 4000 instances 5.56 -> 5.46, a batch of eight 400k-triangle renders 2.50 ->
-// 2.44; host build of 2M triangles as before).  At 1k to 40k the two are even.
-// A room of 36 triangles is bound by the longest path through the tree
-// instead, which opening by area keeps shorter (256 x 256: 86 us, planned 94).
+// 2.44; host build of 2M triangles as before).  At 1k to 40k the two are even,
+// and soups of 24 to 511 triangles have 1 to 3 % less too (256 x 256, 2
+// samples: 200 triangles 1095 -> 1071 us, 300 1223 -> 1249, 511 2294 -> 2221).
+// But a closed box of 36 triangles is bound by the longest path through the
+// tree, which opening by area keeps shorter (256 x 256: 207 us, planned 215;
+// 1280 x 720: 526, 541), so rooms of a few objects stay below the line.
 // A planned tree is no deeper than the one opened by area: where it would be
 // (one or two levels, up to four in a triangle soup), nodes are opened by area
 // on the way.  The stacks of all lanes, and with them the workspaces and

@@ -73,7 +73,6 @@ PT_DEV f3 normalize3(f3 a) {
     float s = 1.0f / sqrtf(dot3(a, a));
     return scl3(a, s);
 }
-PT_DEV float comp3(f3 a, int i) { return i == 0 ? a.x : (i == 1 ? a.y : a.z); }
 PT_DEV f3 xyz(float4 v) { return mk3(v.x, v.y, v.z); }
 PT_DEV float max3c(f3 a) {
     float m = a.x > a.y ? a.x : a.y;
@@ -411,7 +410,7 @@ struct TravStack {
 };
 
 // lds: the block's stack memory (device) or this lane's entries (host: one
-// lane, LDS + 1 entries);
+// lane, LDS + 1 entries); the second argument is not used;
 // gbl: the spill area, where this lane's entry LDS + k is gbl[glane + k * gstride]
 template <int LDS, bool COUNT = false>
 PT_DEV TravStack<LDS, COUNT> make_trav_stack(uint2* lds, int /*lstride*/, uint2* gbl, uint32_t glane, int gstride,
