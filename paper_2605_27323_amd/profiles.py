@@ -28,8 +28,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 # kernel sources: counters taken before a change of these no longer
 # describe the kernels
-SOURCES = ["device.h", "wavefront.h", "wave.h", "kernels.hip", "kernels.h", "ptmi_internal.h", "adjoint.h",
-           "adjoint.hip"]
+SOURCES = ["device.h", "wavefront.h", "wave.h", "small.h", "kernels.hip", "kernels.h", "ptmi_internal.h", "adjoint.h",
+           "adjoint.hip", "batch.h", "batch.hip"]
 N_XCD, N_CU, SIMD_PER_CU = 8, 256, 4
 
 
@@ -188,7 +188,7 @@ def _f(v, fmt="{:.2f}"):
 def markdown(p):
     L = [f"# {p['title']}", "",
          f"Kernel sources hash ({', '.join(SOURCES)}): `{p['source_hash']}`", "",
-         "Commands (on the MI355X box, run from /tmp with TMPDIR=/tmp; R = repository root):", "", "```"]
+         "Commands (on an MI355X, TMPDIR=/tmp; R = repository root, OUT and DIR: output folders):", "", "```"]
     L += p["commands"] + ["```", ""]
     L += ["Calibration with a device copy of "
           f"{p['copy_kib']:.0f} KiB (`__amd_rocclr_copyBuffer`): FETCH_SIZE reads {_f(p['copy_fetch_kib'], '{:.1f}')}"
