@@ -2,7 +2,9 @@
 sized for a larger frame, or for the same frame with per-stage timing): taken
 as ever, the same images and gradients as in a workspace of the size asked
 for; and small frames with more chunks of paths than workgroups, whose spill
-areas bound them: every launch shape gives the stages' image bit for bit."""
+areas bound them: every launch shape gives the stages' image bit for bit.  And
+pt_render_frame_noalloc with the default launch shape on scenes whose tree has
+just the levels that its scratch holds stacks for."""
 import ctypes as C
 
 import numpy as np
@@ -92,3 +94,14 @@ def test_more_chunks_than_workgroups(renderers, which, mode, shape, size):
     ref = R.render(flags=ptmi.FLAG_PROFILE, **kw)
     assert np.array_equal(_bits(img), _bits(ref))
     assert rays == (R.stats()["extension_rays"], R.stats()["shadow_rays"])
+
+
+@pytest.mark.parametrize("seed,n_objects", [(1, 4), (2, 2)])
+@pytest.mark.parametrize("size", [(40, 30), (800, 700)])
+def test_noalloc_with_default_shape(seed, n_objects, size):
+    w, h = size  # a small frame, and one of the megakernel (560000 paths)
+    scene, cam = scenes.procedural(seed=seed, n_objects=n_objects, width=w, height=h)
+    R = ptmi.Renderer(scene, cam)
+    print("noalloc", seed, n_objects, size, R.info.stack_entries, flush=True)
+    kw = dict(spp=1, max_depth=4, rr_start=2, seed=6)
+    assert np.array_equal(_bits(R.render_noalloc(**kw)), _bits(R.render(mode="mega", **kw)))
